@@ -381,12 +381,9 @@ losa_status losa_construct(const void* q, const void* k, const void* v, losa_dty
                 losa::kSparseFwdMaxNk);
   hipStream_t hs = static_cast<hipStream_t>(stream);
   if (dtype == LOSA_DTYPE_F32) {
-    // fp32: the calibration kernel's own two sweeps, then the dense forward
-    st = losa_calibrate_mass(q, k, dtype, B, H, N, d, block_q, block_k, scale, mass, lse,
-                             nullptr, 0, stream);
-    if (st != LOSA_OK) return st;
-    return hip_status(losa::launch_sparse_fwd_f32(d, block_q, block_k, q, k, v, B, H, N, s.n_pad,
-                                                  scale, nullptr, nullptr, 0, o, nullptr, hs),
+    // fp32: two sweeps over the keys for the masses, then the dense forward
+    return hip_status(losa::launch_construct_f32(d, block_q, block_k, q, k, v, B, H, N, s.n_pad,
+                                                 scale, o, mass, lse, hs),
                       "losa_construct");
   }
   // bf16: the dense forward writes O, lse and the block statistics; the masses

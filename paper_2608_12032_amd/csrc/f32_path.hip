@@ -1,26 +1,42 @@
 // fp32 inputs: block masses (Sec. 3.1, Eq. (1)) and frozen-support attention
-// (Sec. 4.2, Eq. (4)) with fp32 vector arithmetic throughout.
+// (Sec. 4.2, Eq. (4)) on the fp32 matrix instructions (fp32 products, fp32
+// accumulation; no input is rounded).
 //
-// fp32 is the small-workload path (no bf16 rounding anywhere), so these
-// kernels keep to a plain per-thread layout: one thread holds one query row
-// (its scaled q and its running output in registers), one workgroup owns one
-// query block of BLK rows, and key/value rows are staged through LDS in chunks
-// of 32 keys that every thread reads as broadcasts.  The workgroup holds KS
-// copies of the block's rows (512 threads at d = 64, 256 at d = 128): copy s
-// takes the row's s-th, (s+KS)-th, ... key block, and the KS partial softmax
-// states (running max, sum, output) are merged in a fixed order at the end, so
-// a row's keys are worked through by KS threads instead of one.  Masking and
-// padding follow the bf16 kernels: keys >= N never enter a softmax, query rows
-// >= N read Q as 0 and get O = 0 and lse = -inf, and so do rows whose key set
-// is empty; col_idx entries outside [0, n_k) are ignored, a repeated entry
-// counts once (the row's ids are flagged in LDS and listed in ascending
-// order), and row bounds are clamped to [0, col_idx_len].
+// Tiles.  A wave owns M query rows (32, or 16 for small calls) and walks
+// 32-key sub-tiles.  It computes S^T = K Q^T, so that a lane holds scores of
+// ONE query (column = lane % M) and the online softmax is in-lane plus an
+// exchange between the lane groups (lane / M), and O^T = V^T P^T, whose B
+// operand of k-step t is register t of the score tile as it stands:
+//   score register t of lane group g  <->  key (t/4) * 4G + 4g + t%4,  G = 64/M.
+// The contraction order over d is free, so lane group g takes
+// d = 4 (G i + g) .. + 3 and one 16-byte load of a K row feeds four matrix
+// instructions; row m of O^T block b stands for d = VC (M (b / VC) + m) + b % VC,
+// VC = 4 (2 at d = 64, M = 32), so a load of VC floats feeds VC d blocks.  K and V go from global
+// memory straight to registers: a 32-key sub-tile is 32 KiB for 8,192
+// matrix cycles (M = 32, d = 128), 16 bytes per clock and CU (32 at M = 16),
+// so staging in LDS would save nothing.  A sub-tile's loads form one stream, K
+// then V, and run kLead loads ahead of the products that use them, across
+// sub-tiles.//
+// Split.  The waves of a workgroup share the M rows and take the row's
+// sub-tiles in turn; their softmax states (max, sum, O) are merged in a fixed
+// order through LDS at the end; two waves per SIMD cover each other's softmax.
 //
-// Row sums.  The softmax normaliser is summed per 32-key chunk in fp32 and the
-// chunk sums are carried in an fp64 running sum (and merged in fp64).  Added
-// one by one to an fp32 accumulator, the many small terms of far keys fall
-// below half its ulp and are lost: over 131k keys that biases the sum low by
-// ~2e-4.
+// Bound: the fp32 matrix rate (157 TFLOP/s).  Attention over full rows, d =
+// 128: 126 TFLOP/s at N = 8,192 x 4 heads, 121 at 4,096, 96 at 4,480 (the last
+// of five rounds 38 % full), 33 at 512 x 4 (a launch with 128 tiles of one
+// round).  A thread per query row with plain fma and its keys in LDS, which
+// this replaced, ran 7.7 TFLOP/s at N = 4,437 x 4 (5.2 ms, now 0.43).
+//
+// Masking and padding follow the bf16 kernels: keys >= N never enter a
+// softmax, query rows >= N read Q as 0 and get O = 0 and lse = -inf, and so do
+// rows whose key set is empty; col_idx entries outside [0, n_k) are ignored, a
+// repeated entry counts once (the row's ids are flagged in LDS and listed in
+// ascending order), and row bounds are clamped to [0, col_idx_len].
+//
+// Row sums.  The softmax normaliser is summed per lane and sub-tile in fp32
+// and carried in an fp64 running sum (and merged in fp64).  Added one by one
+// to an fp32 accumulator, the many small terms of far keys fall below half
+// its ulp and are lost: over 131k keys that biases the sum low by ~2e-4.
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -28,27 +44,163 @@ namespace losa {
 
 namespace {
 
-constexpr int CK = 32;  // keys per LDS chunk
+constexpr int CK = 32;    // keys per sub-tile
+constexpr int kLead = 8;  // loads in flight ahead of their use, per wave
 
-template <int D, int BLK>
-struct F32Cfg {
-  static constexpr int NT = D == 64 ? 512 : 256;  // threads
-  static constexpr int KS = NT / BLK;             // copies of the block's rows (key splits)
-  static constexpr int BUF = 32768;               // floats of the staging / merge buffer
-  static_assert(KS * 2 * CK * D <= BUF && NT * D <= BUF, "staging and partial outputs fit");
+// Shapes of a wave's tile of M query rows.  A sub-tile's operands arrive as a
+// stream of KC chunks of K (16 bytes a lane), then VN of V (VC floats a lane).
+template <int D, int M>
+struct F32Tile {
+  static constexpr int G = 64 / M;             // lane groups
+  static constexpr int SR = M * M / 64;        // score registers per M-key tile
+  static constexpr int KT = CK / M;            // M-key tiles per sub-tile
+  static constexpr int QI = D / (4 * G);       // 16-byte chunks of a row per lane
+  static constexpr int DB = D / M;             // d blocks of O^T
+  static constexpr int VC = DB >= 4 ? 4 : DB;  // floats per V load
+  static constexpr int VP = DB / VC;           // V loads per score register
+  static constexpr int KC = KT * QI;
+  static constexpr int VN = KT * SR * VP;
+  static_assert(DB % VC == 0, "a lane's part of a V row is whole loads");
+  static_assert(KC % kLead == 0 && VN % kLead == 0, "the stream fills the ring evenly");
 };
 
-// CK consecutive rows of D floats starting at row key0 of src, copied by the
-// nts threads ts = 0..nts-1 of one key split
-template <int D>
-__device__ __forceinline__ void stage_rows(float* dst, const float* src, int key0, int ts,
-                                           int nts) {
-  for (int idx = ts; idx < CK * D / 4; idx += nts) {
-    const int row = idx / (D / 4);
-    const int col = (idx % (D / 4)) * 4;
-    *reinterpret_cast<f32x4_t*>(dst + row * D + col) =
-        *reinterpret_cast<const f32x4_t*>(src + (size_t)(key0 + row) * D + col);
+template <int M>
+struct F32Acc;
+template <>
+struct F32Acc<32> {
+  typedef f32x16_t type;
+  static __device__ __forceinline__ type mfma(float a, float b, type c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
   }
+};
+template <>
+struct F32Acc<16> {
+  typedef f32x4_t type;
+  static __device__ __forceinline__ type mfma(float a, float b, type c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+};
+
+// Key of score register t in lane group g, inside an M-key tile.
+template <int M>
+__device__ __forceinline__ int score_key(int t, int g) {
+  return (t >> 2) * (256 / M) + 4 * g + (t & 3);
+}
+
+// Chunk c of the stream of the sub-tile that starts at key0: rows
+// key0 + kt*M + lane%M of K (chunk i of the row), or a piece of V's row of one
+// score register.
+template <int D, int M>
+__device__ __forceinline__ f32x4_t load_k(const float* K, int key0, int c, int lm, int g) {
+  using T = F32Tile<D, M>;
+  const int kt = c % T::KT, i = c / T::KT;
+  return *reinterpret_cast<const f32x4_t*>(K + (size_t)(key0 + lm) * D + 4 * g + kt * M * D +
+                                           4 * T::G * i);
+}
+template <int D, int M>
+__device__ __forceinline__ f32x4_t load_v(const float* V, int key0, int c, int lm, int g) {
+  using T = F32Tile<D, M>;
+  typedef float vec_t __attribute__((ext_vector_type(T::VC)));
+  const int t = c / T::VP % T::SR, kt = c / T::VP / T::SR;
+  const vec_t y = *reinterpret_cast<const vec_t*>(
+      V + (size_t)(key0 + 4 * g) * D + lm * T::VC + (kt * M + score_key<M>(t, 0)) * D +
+      c % T::VP * T::VC * M);
+  f32x4_t x = f32x4_t{};
+#pragma unroll
+  for (int e = 0; e < T::VC; ++e) x[e] = y[e];
+  return x;
+}
+
+// The query operand, scaled; padding rows (!valid) read as 0, so that their
+// scores stay finite whatever the padding holds.
+template <int D, int M>
+__device__ __forceinline__ void load_q(f32x4_t* qr, const float* Q, int row, int g, bool valid,
+                                       float scale_log2) {
+  using T = F32Tile<D, M>;
+  const float* p = Q + (size_t)row * D + 4 * g;
+#pragma unroll
+  for (int i = 0; i < T::QI; ++i) {
+    const f32x4_t x = *reinterpret_cast<const f32x4_t*>(p + 4 * T::G * i);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) qr[i][e] = valid ? x[e] * scale_log2 : 0.f;
+  }
+}
+
+// Scores of a sub-tile in log2 units: chunk c of K, in ring[c % kLead], against
+// the query operand (two accumulation chains, so that no product waits for the
+// one before it).  issue(c) refills the slot just used.  Keys at or beyond
+// kvalid get -inf.
+template <int D, int M, typename Issue>
+__device__ __forceinline__ void scores(f32x4_t* ring, const f32x4_t* qr, int g, int kvalid,
+                                       typename F32Acc<M>::type* s, Issue&& issue) {
+  using T = F32Tile<D, M>;
+  using A = F32Acc<M>;
+  typename A::type odd[T::KT];
+#pragma unroll
+  for (int kt = 0; kt < T::KT; ++kt) {
+    s[kt] = typename A::type{};
+    odd[kt] = typename A::type{};
+  }
+#pragma unroll
+  for (int c = 0; c < T::KC; ++c) {
+    const int kt = c % T::KT, i = c / T::KT;
+    const f32x4_t a = ring[c % kLead];
+    s[kt] = A::mfma(a[0], qr[i][0], s[kt]);
+    odd[kt] = A::mfma(a[1], qr[i][1], odd[kt]);
+    s[kt] = A::mfma(a[2], qr[i][2], s[kt]);
+    odd[kt] = A::mfma(a[3], qr[i][3], odd[kt]);
+    issue(c);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int kt = 0; kt < T::KT; ++kt) s[kt] += odd[kt];
+  if (kvalid < CK) {
+#pragma unroll
+    for (int kt = 0; kt < T::KT; ++kt)
+#pragma unroll
+      for (int t = 0; t < T::SR; ++t)
+        if (kt * M + score_key<M>(t, g) >= kvalid) s[kt][t] = -INFINITY;
+  }
+}
+
+template <int M>
+__device__ __forceinline__ float group_max(float x) {
+  x = fmaxf(x, __shfl_xor(x, 32));
+  if constexpr (M == 16) x = fmaxf(x, __shfl_xor(x, 16));
+  return x;
+}
+template <int M>
+__device__ __forceinline__ double group_sum(double x) {
+  x += __shfl_xor(x, 32);
+  if constexpr (M == 16) x += __shfl_xor(x, 16);
+  return x;
+}
+
+// Maximum of the sub-tile's scores of this lane's query.
+template <int D, int M>
+__device__ __forceinline__ float tile_max(const typename F32Acc<M>::type* s) {
+  using T = F32Tile<D, M>;
+  float mx = s[0][0];
+#pragma unroll
+  for (int kt = 0; kt < T::KT; ++kt)
+#pragma unroll
+    for (int t = 0; t < T::SR; ++t) mx = fmaxf(mx, s[kt][t]);
+  return group_max<M>(mx);
+}
+
+// s <- 2^(s - m); returns this lane's sum.
+template <int D, int M>
+__device__ __forceinline__ float tile_exp(typename F32Acc<M>::type* s, float m) {
+  using T = F32Tile<D, M>;
+  float part = 0.f;
+#pragma unroll
+  for (int kt = 0; kt < T::KT; ++kt)
+#pragma unroll
+    for (int t = 0; t < T::SR; ++t) {
+      s[kt][t] = fast_exp2(s[kt][t] - m);
+      part += s[kt][t];
+    }
+  return part;
 }
 
 // The row's distinct valid key blocks, ascending, into list (dense: every
@@ -95,257 +247,386 @@ __device__ int block_list(int dense, int n_kv, int n_k, const int32_t* __restric
   return nb;
 }
 
-template <int D, int BLK, int BK>
-__global__ void __launch_bounds__((F32Cfg<D, BLK>::NT))
-    sparse_fwd_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
-                          const float* __restrict__ V, const int32_t* __restrict__ row_ptr,
-                          const int32_t* __restrict__ col_idx, int64_t col_len,
-                          float* __restrict__ O, float* __restrict__ lse, int n_q, int n_k, int N,
-                          int n_pad, float scale_log2, int dense) {
-  using C = F32Cfg<D, BLK>;
-  __shared__ __attribute__((aligned(16))) float buf[C::BUF];
+constexpr int kF32Waves = 8;  // waves of a workgroup (key splits): two per SIMD
+
+// Attention of M query rows over their query block's key blocks (bk_sub
+// 32-key sub-tiles each).  PV: O and, if given, lse (natural log).  !PV: only
+// the normaliser, in log2 units, to lse (dense).
+template <int D, int M, bool PV>
+__global__ void __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(2)))
+    attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+                    const float* __restrict__ V, const int32_t* __restrict__ row_ptr,
+                    const int32_t* __restrict__ col_idx, int64_t col_len, float* __restrict__ O,
+                    float* __restrict__ lse, int blk, int bk_sub, int n_k, int N, int n_pad,
+                    float scale_log2, int dense) {
+  using T = F32Tile<D, M>;
+  using A = F32Acc<M>;
+  constexpr int NWV = kF32Waves;
+  constexpr int NT = 64 * NWV;
+  constexpr int LD = D + 4;  // floats of a row of a partial output in LDS
   __shared__ uint8_t flag[kSparseFwdMaxNk];
   __shared__ uint16_t list[kSparseFwdMaxNk];
-  __shared__ int wcount[C::NT / 64];
-  __shared__ float mpart[C::NT];
-  __shared__ double lpart[C::NT];
+  __shared__ int wcount[NWV];
+  __shared__ float mpart[NWV * M];
+  __shared__ double lpart[NWV * M];
+  __shared__ __attribute__((aligned(16))) float opart[PV ? NWV * M * LD : 4];
   const int tid = threadIdx.x;
-  const int sp = tid / BLK;  // key split
-  const int t = tid % BLK;   // row of the block
-  const int r = blockIdx.x;
-  const int bh = r / n_q;
-  const int i = r - bh * n_q;
+  const int lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lm = lane % M, g = lane / M;
+  const int tiles = n_pad / M;  // per head
+  const int x0 = xcd_remap(blockIdx.x, gridDim.x);
+  const int bh = x0 / tiles;
+  const int row0 = (x0 - bh * tiles) * M;
+  const int r = bh * (n_pad / blk) + row0 / blk;
   const size_t head = (size_t)bh * n_pad * D;
-  const int qrow = i * BLK + t;
-
-  // padding query rows take Q = 0: their scores stay finite whatever the
-  // padding holds (their output is written as 0 at the end)
+  const int qrow = row0 + lm;
   const bool qvalid = qrow < N;
-  float q[D], o[D];
-#pragma unroll
-  for (int dd = 0; dd < D; ++dd) {
-    q[dd] = qvalid ? Q[head + (size_t)qrow * D + dd] * scale_log2 : 0.f;
-    o[dd] = 0.f;
-  }
+
+  f32x4_t qr[T::QI];
+  load_q<D, M>(qr, Q + head, qrow, g, qvalid, scale_log2);
+  const int bk = bk_sub * CK;
+  const int nb = block_list<NT>(dense, (N + bk - 1) / bk, n_k, row_ptr, col_idx, col_len, r, flag,
+                                list, wcount);
+  const int S = nb * bk_sub;
+  auto key_of = [&](int x) -> int {
+    const int y = x < S ? x : S - 1;
+    const int j = y / bk_sub;
+    return __builtin_amdgcn_readfirstlane((int)list[j]) * bk + (y - j * bk_sub) * CK;
+  };
+
   float m = kNegBig;
   double l = 0.0;
-
-  const int nb = block_list<C::NT>(dense, (N + BK - 1) / BK, n_k, row_ptr, col_idx, col_len, r,
-                                   flag, list, wcount);
-  float* Kc = buf + sp * 2 * CK * D;
-  float* Vc = Kc + CK * D;
-  const int rounds = (nb + C::KS - 1) / C::KS;
-  for (int rd = 0; rd < rounds; ++rd) {
-    const int x = rd * C::KS + sp;
-    const int j = x < nb ? (int)list[x] : 0;
-    const int kvalid = x < nb ? min(BK, N - j * BK) : 0;
-    for (int c0 = 0; c0 < BK; c0 += CK) {  // the same trip count in every split
-      __syncthreads();
-      const bool live = c0 < kvalid;
-      if (live) {
-        stage_rows<D>(Kc, K + head, j * BK + c0, t, BLK);
-        stage_rows<D>(Vc, V + head, j * BK + c0, t, BLK);
-      }
-      __syncthreads();
-      if (!live) continue;  // the same for every thread of the split
-      const int nk = min(CK, kvalid - c0);
-      float s[CK];
-      float mx = m;
+  typename A::type o[T::DB];
+  if constexpr (PV) {
 #pragma unroll
-      for (int kk = 0; kk < CK; ++kk) {
-        float acc = 0.f;
+    for (int b = 0; b < T::DB; ++b) o[b] = typename A::type{};
+  }
+  constexpr int NC = T::KC + (PV ? T::VN : 0);  // chunks of a sub-tile
+  const float* Kh = K + head;
+  const float* Vh = V + head;
+  f32x4_t ring[kLead];
+  int key0 = 0;
+  if (w < S) {
+    key0 = key_of(w);
 #pragma unroll
-        for (int dd = 0; dd < D; ++dd) acc = fmaf(q[dd], Kc[kk * D + dd], acc);
-        s[kk] = kk < nk ? acc : -INFINITY;
-        mx = fmaxf(mx, s[kk]);
-      }
-      const float alpha = fast_exp2(m - mx);
-      m = mx;
+    for (int c = 0; c < kLead; ++c) ring[c] = load_k<D, M>(Kh, key0, c, lm, g);
+  }
+  for (int x = w; x < S; x += NWV) {
+    const int next = key_of(x + NWV);  // past the end: the last sub-tile again
+    // chunk c's slot takes chunk c + kLead of the stream
+    auto issue = [&](int c) {
+      const int n = c + kLead;
+      if (n < T::KC)
+        ring[c % kLead] = load_k<D, M>(Kh, key0, n, lm, g);
+      else if (n < NC)
+        ring[c % kLead] = load_v<D, M>(Vh, key0, n - T::KC, lm, g);
+      else
+        ring[c % kLead] = load_k<D, M>(Kh, next, n - NC, lm, g);
+    };
+    typename A::type s[T::KT];
+    scores<D, M>(ring, qr, g, N - key0, s, issue);
+    const float mx = tile_max<D, M>(s);
+    if (__ballot(mx > m) != 0) {
+      const float m_new = fmaxf(m, mx);
+      const float alpha = fast_exp2(m - m_new);
+      m = m_new;
       l *= (double)alpha;
+      if constexpr (PV) {
 #pragma unroll
-      for (int dd = 0; dd < D; ++dd) o[dd] *= alpha;
-      float part = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < CK; ++kk) {
-        const float p = fast_exp2(s[kk] - m);
-        part += p;
-#pragma unroll
-        for (int dd = 0; dd < D; ++dd) o[dd] = fmaf(p, Vc[kk * D + dd], o[dd]);
+        for (int b = 0; b < T::DB; ++b) o[b] *= alpha;
       }
-      l += (double)part;
+    }
+    l += (double)tile_exp<D, M>(s, m);
+    if constexpr (PV) {
+#pragma unroll
+      for (int c = 0; c < T::VN; ++c) {
+        const int p = c % T::VP, t = c / T::VP % T::SR, kt = c / T::VP / T::SR;
+        const f32x4_t a = ring[(T::KC + c) % kLead];
+#pragma unroll
+        for (int e = 0; e < T::VC; ++e)
+          o[p * T::VC + e] = A::mfma(a[e], s[kt][t], o[p * T::VC + e]);
+        issue(T::KC + c);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    key0 = next;
+  }
+
+  // merge the waves' states: the common max, then sums and outputs rescaled to
+  // it, added in wave order
+  const double lw = group_sum<M>(l);
+  if (g == 0) {
+    mpart[w * M + lm] = m;
+    lpart[w * M + lm] = lw;
+  }
+  if constexpr (PV) {
+    // register t of d block b holds d = VC * (M (b / VC) + row) + b % VC
+#pragma unroll
+    for (int t = 0; t < T::SR; ++t)
+#pragma unroll
+      for (int b = 0; b < T::DB; ++b)
+        opart[(w * M + lm) * LD + T::VC * (b / T::VC * M + score_key<M>(t, g)) + b % T::VC] =
+            o[b][t];
+  }
+  __syncthreads();
+  auto merged = [&](int row, float* wgt) -> double {  // sum of row `row`, weight of each wave
+    float mm = kNegBig;
+#pragma unroll
+    for (int y = 0; y < NWV; ++y) mm = fmaxf(mm, mpart[y * M + row]);
+    double lt = 0.0;
+#pragma unroll
+    for (int y = 0; y < NWV; ++y) {
+      wgt[y] = fast_exp2(mpart[y * M + row] - mm);
+      lt += lpart[y * M + row] * (double)wgt[y];
+    }
+    wgt[NWV] = mm;
+    return lt;
+  };
+  float wgt[NWV + 1];
+  if (tid < M && lse != nullptr) {
+    const float lf = (float)merged(tid, wgt);
+    const float l2 = wgt[NWV] + __log2f(lf);
+    const bool ok = row0 + tid < N && lf > 0.f;
+    lse[(size_t)bh * n_pad + row0 + tid] = PV ? (ok ? l2 * kLn2 : -INFINITY) : l2;
+  }
+  if constexpr (PV) {
+    for (int idx = tid; idx < M * D / 4; idx += NT) {
+      const int row = idx / (D / 4), d4 = (idx % (D / 4)) * 4;
+      const float lf = (float)merged(row, wgt);
+      const float inv = (row0 + row < N && lf > 0.f) ? 1.0f / lf : 0.f;
+      f32x4_t acc = f32x4_t{};
+#pragma unroll
+      for (int y = 0; y < NWV; ++y) {
+        const f32x4_t p = *reinterpret_cast<const f32x4_t*>(opart + (y * M + row) * LD + d4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = fmaf(p[e], wgt[y], acc[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] *= inv;
+      *reinterpret_cast<f32x4_t*>(O + head + (size_t)(row0 + row) * D + d4) = acc;
     }
   }
-
-  // merge the KS partial states of each row in split order: the common max,
-  // then the sums and outputs rescaled to it.  Partial outputs go to LDS
-  // d-major, so consecutive threads write consecutive words.
-  __syncthreads();  // every split is done with its staging buffers
-  mpart[tid] = m;
-  lpart[tid] = l;
-#pragma unroll
-  for (int dd = 0; dd < D; ++dd) buf[dd * C::NT + tid] = o[dd];
-  __syncthreads();
-  if (sp != 0) return;
-  float M = kNegBig;
-  for (int s2 = 0; s2 < C::KS; ++s2) M = fmaxf(M, mpart[s2 * BLK + t]);
-  float wgt[C::KS];
-  double lt = 0.0;
-#pragma unroll
-  for (int s2 = 0; s2 < C::KS; ++s2) {
-    wgt[s2] = fast_exp2(mpart[s2 * BLK + t] - M);
-    lt += lpart[s2 * BLK + t] * (double)wgt[s2];
-  }
-  const float lf = (float)lt;
-  const bool ok = qvalid && (lf > 0.f);
-  const float inv = ok ? 1.0f / lf : 0.f;
-#pragma unroll
-  for (int dd = 0; dd < D; ++dd) {
-    float acc = 0.f;
-#pragma unroll
-    for (int s2 = 0; s2 < C::KS; ++s2) acc = fmaf(buf[dd * C::NT + s2 * BLK + t], wgt[s2], acc);
-    O[head + (size_t)qrow * D + dd] = acc * inv;
-  }
-  if (lse != nullptr) lse[(size_t)bh * n_pad + qrow] = ok ? (M + __log2f(lf)) * kLn2 : -INFINITY;
 }
 
-template <int D, int BLK, int BK>
-__global__ void __launch_bounds__((F32Cfg<D, BLK>::NT))
-    calib_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
-                     float* __restrict__ mass, float* __restrict__ lse, int n_q, int n_k, int N,
-                     int n_pad, float scale_log2) {
-  using C = F32Cfg<D, BLK>;
-  constexpr int WPS = BLK / 64;  // waves per key split
-  __shared__ __attribute__((aligned(16))) float buf[C::KS * CK * D];
-  __shared__ float mpart[C::NT];
-  __shared__ double lpart[C::NT];
-  __shared__ float red[C::NT / 64];
+// Block masses of one query block (blockIdx.x) over a range of per_wg key
+// blocks (blockIdx.y).  Four waves: BLK/32 of them own 32 query rows each, and
+// with 64-row blocks two such pairs take the key blocks in turn.  lse2 (log2
+// units) comes from attn_f32_kernel, or (OWN: the caller gives no buffer to
+// hold it; one workgroup per query block) from a first sweep over the keys.
+template <int D, int BLK, bool OWN>
+__global__ void __launch_bounds__(256)
+    mass_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+                    const float* __restrict__ lse2_in, float* __restrict__ mass, int bk_sub,
+                    int per_wg, int n_k, int N, int n_pad, float scale_log2) {
+  constexpr int M = 32;
+  constexpr int RW = BLK / M;   // row waves
+  constexpr int KSP = 4 / RW;   // waves that share rows and split the keys
+  using T = F32Tile<D, M>;
+  using A = F32Acc<M>;
+  __shared__ float mpart[4 * M];
+  __shared__ double lpart[4 * M];
+  __shared__ float part[4];
   const int tid = threadIdx.x;
-  const int sp = tid / BLK;
-  const int t = tid % BLK;
   const int lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rw = w % RW, sp = w / RW;
+  const int lm = lane % M, g = lane / M;
+  const int n_q = n_pad / BLK;
   const int r = blockIdx.x;
   const int bh = r / n_q;
   const int i = r - bh * n_q;
   const size_t head = (size_t)bh * n_pad * D;
-  const int qrow = i * BLK + t;
   const int rows_valid = min(BLK, N - i * BLK);
+  const int bk = bk_sub * CK;
+  const int j0 = blockIdx.y * per_wg, j1 = min(n_k, j0 + per_wg);
   float* mrow = mass + (size_t)r * n_k;
-  if (rows_valid <= 0) {
-    for (int j = tid; j < n_k; j += C::NT) mrow[j] = 0.f;
-    if (lse != nullptr && sp == 0) lse[(size_t)bh * n_pad + qrow] = -INFINITY;
+  if (rows_valid <= 0) {  // a query block made only of padding
+    for (int j = j0 + tid; j < j1; j += 256) mrow[j] = 0.f;
     return;
   }
-  // padding query rows take Q = 0 (finite scores whatever the padding holds;
-  // they are never read into a mass)
+  const int qrow = i * BLK + rw * M + lm;
   const bool qvalid = qrow < N;
-  float q[D];
+  f32x4_t qr[T::QI];
+  load_q<D, M>(qr, Q + head, qrow, g, qvalid, scale_log2);
+  const float* Kh = K + head;
+  f32x4_t ring[kLead];
+  typename A::type s[T::KT];
+  // first chunks of the sub-tile at key0, and the refill while it is worked on
+  // (its own later chunks, then the first of the one at `next`)
+  auto lead = [&](int key0) {
 #pragma unroll
-  for (int dd = 0; dd < D; ++dd) q[dd] = qvalid ? Q[head + (size_t)qrow * D + dd] * scale_log2 : 0.f;
-  const int n_kv = (N + BK - 1) / BK;  // key blocks holding a real key; split s takes s, s+KS, ...
-  const int rounds = (n_kv + C::KS - 1) / C::KS;
-  float* Kc = buf + sp * CK * D;
+    for (int c = 0; c < kLead; ++c) ring[c] = load_k<D, M>(Kh, key0, c, lm, g);
+  };
+  auto sub_scores = [&](int key0, int next) {
+    scores<D, M>(ring, qr, g, N - key0, s, [&](int c) {
+      const int n = c + kLead;
+      ring[c % kLead] = load_k<D, M>(Kh, n < T::KC ? key0 : next, n % T::KC, lm, g);
+    });
+  };
 
-  // sweep 1: running max / sum over this split's keys, then merged over the
-  // splits in split order (every thread merges its row, so all splits hold it)
-  float m = kNegBig;
-  double l = 0.0;
-  for (int rd = 0; rd < rounds; ++rd) {
-    const int j = rd * C::KS + sp;
-    const int kvalid = j < n_kv ? min(BK, N - j * BK) : 0;
-    for (int c0 = 0; c0 < BK; c0 += CK) {
-      __syncthreads();
-      const bool live = c0 < kvalid;
-      if (live) stage_rows<D>(Kc, K + head, j * BK + c0, t, BLK);
-      __syncthreads();
-      if (!live) continue;
-      const int nk = min(CK, kvalid - c0);
-      float s[CK];
-      float mx = m;
-#pragma unroll
-      for (int kk = 0; kk < CK; ++kk) {
-        float acc = 0.f;
-#pragma unroll
-        for (int dd = 0; dd < D; ++dd) acc = fmaf(q[dd], Kc[kk * D + dd], acc);
-        s[kk] = kk < nk ? acc : -INFINITY;
-        mx = fmaxf(mx, s[kk]);
-      }
-      l *= (double)fast_exp2(m - mx);
-      m = mx;
-      float part = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < CK; ++kk) part += fast_exp2(s[kk] - m);
-      l += (double)part;
+  float lse2;
+  if constexpr (OWN) {
+    float m = kNegBig;
+    double l = 0.0;
+    const int S = (N + CK - 1) / CK;
+    if (sp < S) lead(sp * CK);
+    for (int x = sp; x < S; x += KSP) {
+      sub_scores(x * CK, (x + KSP < S ? x + KSP : x) * CK);
+      const float m_new = fmaxf(m, tile_max<D, M>(s));
+      l *= (double)fast_exp2(m - m_new);
+      m = m_new;
+      l += (double)tile_exp<D, M>(s, m);
     }
+    l = group_sum<M>(l);
+    if (g == 0) {
+      mpart[w * M + lm] = m;
+      lpart[w * M + lm] = l;
+    }
+    __syncthreads();
+    float mm = kNegBig;
+#pragma unroll
+    for (int y = 0; y < KSP; ++y) mm = fmaxf(mm, mpart[(y * RW + rw) * M + lm]);
+    double lt = 0.0;
+#pragma unroll
+    for (int y = 0; y < KSP; ++y)
+      lt += lpart[(y * RW + rw) * M + lm] *
+            (double)fast_exp2(mpart[(y * RW + rw) * M + lm] - mm);
+    lse2 = mm + __log2f((float)lt);
+  } else {
+    lse2 = lse2_in[(size_t)bh * n_pad + qrow];
   }
-  mpart[tid] = m;
-  lpart[tid] = l;
-  __syncthreads();
-  float M = kNegBig;
-  for (int s2 = 0; s2 < C::KS; ++s2) M = fmaxf(M, mpart[s2 * BLK + t]);
-  double lt = 0.0;
-  for (int s2 = 0; s2 < C::KS; ++s2)
-    lt += lpart[s2 * BLK + t] * (double)fast_exp2(mpart[s2 * BLK + t] - M);
-  const float lse2 = M + __log2f((float)lt);
-  if (lse != nullptr && sp == 0) lse[(size_t)bh * n_pad + qrow] = qvalid ? lse2 * kLn2 : -INFINITY;
+  // padding rows (Q = 0, finite scores) contribute exp2(-inf) = 0 to every mass
   const float sub = qvalid ? lse2 : INFINITY;
 
-  // sweep 2: per key block of this split, the normalised probabilities summed
-  // over the block's keys and the query block's rows (waves of the split added
-  // in order)
+  // this wave's key blocks: j0 + sp, j0 + sp + KSP, ...; the trip count is the
+  // same for every wave (barriers inside)
   const float inv_rows = 1.0f / (float)rows_valid;
-  for (int rd = 0; rd < rounds; ++rd) {
-    const int j = rd * C::KS + sp;
-    const int kvalid = j < n_kv ? min(BK, N - j * BK) : 0;
+  const int trips = (j1 - j0 + KSP - 1) / KSP;
+  auto sub_key = [&](int y) -> int {  // first key of this wave's y-th sub-tile
+    const int c = y / bk_sub;
+    return (j0 + sp + c * KSP) * bk + (y - c * bk_sub) * CK;
+  };
+  // (a key block at or past j1 is not this workgroup's: nothing is read; the
+  // refill past the last sub-tile reads the current one again)
+  const int mine = max(0, (j1 - j0 - sp + KSP - 1) / KSP) * bk_sub;  // sub-tiles of this wave
+  if (mine > 0) lead(sub_key(0));
+  for (int c = 0; c < trips; ++c) {
+    const int j = j0 + sp + c * KSP;
     float acc = 0.f;
-    for (int c0 = 0; c0 < BK; c0 += CK) {
-      __syncthreads();
-      const bool live = c0 < kvalid;
-      if (live) stage_rows<D>(Kc, K + head, j * BK + c0, t, BLK);
-      __syncthreads();
-      if (!live) continue;
-      const int nk = min(CK, kvalid - c0);
-#pragma unroll
-      for (int kk = 0; kk < CK; ++kk) {
-        float s = 0.f;
-#pragma unroll
-        for (int dd = 0; dd < D; ++dd) s = fmaf(q[dd], Kc[kk * D + dd], s);
-        acc += kk < nk ? fast_exp2(s - sub) : 0.f;
-      }
+    for (int u = 0; u < bk_sub; ++u) {
+      const int y = c * bk_sub + u;
+      if (y >= mine || sub_key(y) >= N) continue;
+      const int next = y + 1 < mine ? sub_key(y + 1) : 0;
+      sub_scores(sub_key(y), next < N ? next : 0);
+      acc += tile_exp<D, M>(s, sub);
     }
     acc = wave_sum(acc);
-    if (lane == 0) red[tid >> 6] = acc;
+    if (lane == 0) part[w] = acc;
     __syncthreads();
-    if (t == 0 && j < n_kv) {
+    if (lane == 0 && rw == 0 && j < j1) {
       float tot = 0.f;
-      for (int ww = 0; ww < WPS; ++ww) tot += red[sp * WPS + ww];
+#pragma unroll
+      for (int y = 0; y < RW; ++y) tot += part[sp * RW + y];
       mrow[j] = tot * inv_rows;
     }
+    __syncthreads();
   }
-  for (int j = n_kv + tid; j < n_k; j += C::NT) mrow[j] = 0.f;
 }
 
-template <int D, int BLK, int BK>
-hipError_t launch_f32(const void* q, const void* k, const void* v, int B, int H, int N, int n_pad,
-                      float scale, const int32_t* row_ptr, const int32_t* col_idx,
-                      int64_t col_len, void* o, float* lse, int dense, hipStream_t stream) {
-  const int n_q = n_pad / BLK, n_k = n_pad / BK;
-  hipLaunchKernelGGL((sparse_fwd_f32_kernel<D, BLK, BK>), dim3(B * H * n_q),
-                     dim3(F32Cfg<D, BLK>::NT), 0, stream,
-                     static_cast<const float*>(q), static_cast<const float*>(k),
-                     static_cast<const float*>(v), row_ptr, col_idx, col_len,
-                     static_cast<float*>(o), lse, n_q, n_k, N, n_pad, scale * kLog2e, dense);
+// log2 normalisers -> natural logs, -inf on padding rows.
+__global__ void __launch_bounds__(256)
+    lse_natural_kernel(float* __restrict__ lse, int N, int n_pad, int64_t total) {
+  const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (x < total) lse[x] = x % n_pad < N ? lse[x] * kLn2 : -INFINITY;
+}
+
+// Tile height of a call with `tiles` 32-row tiles.  A workgroup fills a CU and
+// a row's keys are not split over workgroups, so the time goes in rounds of
+// 256 tiles; a round of 16-row tiles has half the work but the same K/V
+// traffic.  Measured, one round of 32-row against one of 16-row tiles: 79 /
+// 44 us at d = 128 and 48 / 25 us at d = 64 (N = 2,048, 4 heads), scores only 79 / 64
+// us (N = 4,437, d = 128).  So at 560 tiles attention takes 16 rows (428
+// against 455 us) and at 512 it takes 32 (284 against 319 us).
+template <bool PV>
+bool wide_tiles(int64_t tiles) {
+  const int64_t r32 = (tiles + 255) / 256, r16 = (2 * tiles + 255) / 256;
+  return PV ? 19 * r32 <= 10 * r16 : 5 * r32 <= 4 * r16;
+}
+
+template <int D, int M, bool PV>
+hipError_t launch_attn(const void* q, const void* k, const void* v, int BH, int blk, int blk_k,
+                       int N, int n_pad, float scale, const int32_t* row_ptr,
+                       const int32_t* col_idx, int64_t col_len, void* o, float* lse,
+                       hipStream_t stream) {
+  hipLaunchKernelGGL((attn_f32_kernel<D, M, PV>), dim3(BH * (n_pad / M)),
+                     dim3(64 * kF32Waves), 0, stream, static_cast<const float*>(q),
+                     static_cast<const float*>(k), static_cast<const float*>(v), row_ptr, col_idx,
+                     col_len, static_cast<float*>(o), lse, blk, blk_k / CK, n_pad / blk_k, N,
+                     n_pad, scale * kLog2e, row_ptr == nullptr);
   return hipGetLastError();
 }
 
-template <int D, int BLK, int BK>
-hipError_t launch_cal_f32(const void* q, const void* k, int B, int H, int N, int n_pad, float scale,
-                          float* mass, float* lse, hipStream_t stream) {
-  const int n_q = n_pad / BLK, n_k = n_pad / BK;
-  hipLaunchKernelGGL((calib_f32_kernel<D, BLK, BK>), dim3(B * H * n_q), dim3(F32Cfg<D, BLK>::NT),
-                     0, stream,
-                     static_cast<const float*>(q), static_cast<const float*>(k), mass, lse, n_q,
-                     n_k, N, n_pad, scale * kLog2e);
+template <bool PV>
+hipError_t launch_attn_any(int d, int blk, int blk_k, const void* q, const void* k, const void* v,
+                           int BH, int N, int n_pad, float scale, const int32_t* row_ptr,
+                           const int32_t* col_idx, int64_t col_len, void* o, float* lse,
+                           hipStream_t stream) {
+  const bool wide = wide_tiles<PV>((int64_t)BH * (n_pad / 32));
+#define LOSA_F32_ATTN(DD, MM)                                                                     \
+  if (d == DD && wide == (MM == 32))                                                              \
+    return launch_attn<DD, MM, PV>(q, k, v, BH, blk, blk_k, N, n_pad, scale, row_ptr, col_idx,    \
+                                   col_len, o, lse, stream);
+  LOSA_F32_ATTN(64, 32)
+  LOSA_F32_ATTN(64, 16)
+  LOSA_F32_ATTN(128, 32)
+  LOSA_F32_ATTN(128, 16)
+#undef LOSA_F32_ATTN
+  return hipErrorInvalidValue;
+}
+
+template <int D, int BLK>
+hipError_t launch_mass(const void* q, const void* k, const float* lse2, float* mass, int BH,
+                       int blk_k, int N, int n_pad, float scale, hipStream_t stream) {
+  const int rows = BH * (n_pad / BLK);
+  const int n_k = n_pad / blk_k;
+  const float* qf = static_cast<const float*>(q);
+  const float* kf = static_cast<const float*>(k);
+  if (lse2 == nullptr) {
+    hipLaunchKernelGGL((mass_f32_kernel<D, BLK, true>), dim3(rows, 1), dim3(256), 0, stream, qf,
+                       kf, nullptr, mass, blk_k / CK, n_k, n_k, N, n_pad, scale * kLog2e);
+    return hipGetLastError();
+  }
+  // enough workgroups for four per CU, each with a few key blocks at least
+  const int want = rows < 1024 ? (1024 + rows - 1) / rows : 1;
+  const int least = 256 / blk_k > 1 ? 256 / blk_k : 1;
+  int per_wg = (n_k + want - 1) / want;
+  if (per_wg < least) per_wg = least;
+  hipLaunchKernelGGL((mass_f32_kernel<D, BLK, false>), dim3(rows, (n_k + per_wg - 1) / per_wg),
+                     dim3(256), 0, stream, qf, kf, lse2, mass, blk_k / CK, per_wg, n_k, N, n_pad,
+                     scale * kLog2e);
   return hipGetLastError();
+}
+
+// Masses, given room for the log2 normalisers (one float per token; written
+// here) or none (scratch == nullptr).
+hipError_t masses(int d, int blk, int blk_k, const void* q, const void* k, int BH, int N,
+                  int n_pad, float scale, float* mass, float* scratch, hipStream_t stream) {
+  if (scratch != nullptr) {
+    const hipError_t err =
+        launch_attn_any<false>(d, blk, blk_k, q, k, nullptr, BH, N, n_pad, scale, nullptr, nullptr,
+                               0, nullptr, scratch, stream);
+    if (err != hipSuccess) return err;
+  }
+#define LOSA_F32_MASS(DD, BB)  \
+  if (d == DD && blk == BB)    \
+    return launch_mass<DD, BB>(q, k, scratch, mass, BH, blk_k, N, n_pad, scale, stream);
+  LOSA_F32_MASS(64, 64)
+  LOSA_F32_MASS(64, 128)
+  LOSA_F32_MASS(128, 64)
+  LOSA_F32_MASS(128, 128)
+#undef LOSA_F32_MASS
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -354,39 +635,31 @@ hipError_t launch_sparse_fwd_f32(int d, int blk, int blk_k, const void* q, const
                                  const void* v, int B, int H, int N, int n_pad, float scale,
                                  const int32_t* row_ptr, const int32_t* col_idx, int64_t col_len,
                                  void* o, float* lse, hipStream_t stream) {
-  const int dense = row_ptr == nullptr;  // internal: the construction step's dense attention
-#define LOSA_F32_FWD(DD, BB, KK)                                                               \
-  if (d == DD && blk == BB && blk_k == KK)                                                     \
-    return launch_f32<DD, BB, KK>(q, k, v, B, H, N, n_pad, scale, row_ptr, col_idx, col_len, o, \
-                                  lse, dense, stream);
-  LOSA_F32_FWD(64, 64, 64)
-  LOSA_F32_FWD(64, 128, 128)
-  LOSA_F32_FWD(128, 64, 64)
-  LOSA_F32_FWD(128, 128, 128)
-  LOSA_F32_FWD(64, 64, 32)
-  LOSA_F32_FWD(64, 128, 32)
-  LOSA_F32_FWD(128, 64, 32)
-  LOSA_F32_FWD(128, 128, 32)
-#undef LOSA_F32_FWD
-  return hipErrorInvalidValue;
+  return launch_attn_any<true>(d, blk, blk_k, q, k, v, B * H, N, n_pad, scale, row_ptr, col_idx,
+                               col_len, o, lse, stream);
 }
 
 hipError_t launch_calibrate_f32(int d, int blk, int blk_k, const void* q, const void* k, int B,
                                 int H, int N, int n_pad, float scale, float* mass, float* lse,
                                 hipStream_t stream) {
-#define LOSA_F32_CAL(DD, BB, KK)                                                              \
-  if (d == DD && blk == BB && blk_k == KK)                                                    \
-    return launch_cal_f32<DD, BB, KK>(q, k, B, H, N, n_pad, scale, mass, lse, stream);
-  LOSA_F32_CAL(64, 64, 64)
-  LOSA_F32_CAL(64, 128, 128)
-  LOSA_F32_CAL(128, 64, 64)
-  LOSA_F32_CAL(128, 128, 128)
-  LOSA_F32_CAL(64, 64, 32)
-  LOSA_F32_CAL(64, 128, 32)
-  LOSA_F32_CAL(128, 64, 32)
-  LOSA_F32_CAL(128, 128, 32)
-#undef LOSA_F32_CAL
-  return hipErrorInvalidValue;
+  // the caller's lse holds the log2 normalisers until the masses are formed
+  hipError_t err = masses(d, blk, blk_k, q, k, B * H, N, n_pad, scale, mass, lse, stream);
+  if (err != hipSuccess || lse == nullptr) return err;
+  const int64_t total = (int64_t)B * H * n_pad;
+  hipLaunchKernelGGL(lse_natural_kernel, dim3((uint32_t)((total + 255) / 256)), dim3(256), 0, stream, lse, N,
+                     n_pad, total);
+  return hipGetLastError();
+}
+
+hipError_t launch_construct_f32(int d, int blk, int blk_k, const void* q, const void* k,
+                                const void* v, int B, int H, int N, int n_pad, float scale,
+                                void* o, float* mass, float* lse, hipStream_t stream) {
+  // O is written last: until then its first floats hold the log2 normalisers
+  const hipError_t err = masses(d, blk, blk_k, q, k, B * H, N, n_pad, scale, mass,
+                                static_cast<float*>(o), stream);
+  if (err != hipSuccess) return err;
+  return launch_sparse_fwd_f32(d, blk, blk_k, q, k, v, B, H, N, n_pad, scale, nullptr, nullptr, 0,
+                               o, lse, stream);
 }
 
 }  // namespace losa

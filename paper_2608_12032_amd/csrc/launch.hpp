@@ -54,6 +54,10 @@ hipError_t launch_sparse_fwd_f32(int d, int blk, int blk_k, const void* q, const
                                  const void* v, int B, int H, int N, int n_pad, float scale,
                                  const int32_t* row_ptr, const int32_t* col_idx, int64_t col_len,
                                  void* o, float* lse, hipStream_t stream);
+// construction step: masses, then dense attention (both launches above)
+hipError_t launch_construct_f32(int d, int blk, int blk_k, const void* q, const void* k,
+                                const void* v, int B, int H, int N, int n_pad, float scale,
+                                void* o, float* mass, float* lse, hipStream_t stream);
 size_t sparse_fwd_bf16_workspace(int B, int H, int n_pad, int d, int n_q);
 
 // Recall of a frozen support (Eq. (2)): per row the retained and the total

@@ -1,0 +1,80 @@
+"""fp32 kernels at the edges of their tiles.
+
+The attention kernel works on 32-row tiles or, where that fills the chip
+better (a call of at most 128 of the former, for one), on 16-row tiles; its eight waves share a row's 32-key sub-tiles.  The
+mass kernel splits a row's key blocks over workgroups when the normalisers have
+room (the caller's lse, or the construction step's output) and sweeps the keys
+itself when they have none.  Each combination of tile height, head size, block
+shape and ragged length, with fewer, as many and more sub-tiles than waves,
+against the oracle on every row.  Bars: the fp32 path's (1e-4 on outputs and
+masses, 1e-3 on lse)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import losa_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+# (heads, d, block_q, block_k, N): 16-row tiles, then 32-row ones
+CASES = [(2, 64, 64, 64, 33), (2, 128, 128, 128, 257), (3, 128, 64, 32, 289), (2, 64, 128, 32, 480),
+         (12, 64, 64, 64, 385), (10, 128, 128, 128, 511), (9, 128, 128, 32, 487),
+         (17, 64, 128, 128, 256), (14, 128, 64, 64, 321)]
+
+
+@pytest.fixture(scope="module")
+def L():
+    assert torch.cuda.is_available(), "GPU tests need a visible MI355X"
+    from paper_2608_12032_amd import losa
+    return losa
+
+
+def f64(x):
+    return x.detach().double().cpu().numpy()
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+def test_f32_tiles(L, case):
+    H, d, Cq, Ck, N = case
+    n_pad = O.padded_len(N, Cq, Ck)
+    n_q, n_k = n_pad // Cq, n_pad // Ck
+    print(f"[gpu-f32-tiles] H={H} d={d} blocks={Cq}x{Ck} N={N}", flush=True)
+    g = torch.Generator().manual_seed(700 + CASES.index(case))
+    q, k, v = (torch.randn((1, H, n_pad, d), generator=g) * 1.3 for _ in range(3))
+    q, k, v = q.cuda(), k.cuda(), v.cuda()     # padding rows hold values too
+    scale = 1.0 / np.sqrt(d)
+    qh, kh, vh = f64(q), f64(k), f64(v)
+    m_ref, l_ref = O.block_masses(qh, kh, N, Cq, Ck, scale)
+
+    mass, lse = L.losa_calibrate_mass(q, k, N, Cq, Ck)
+    mass2, none = L.losa_calibrate_mass(q, k, N, Cq, Ck, want_lse=False)
+    o, mass3, lse3 = L.losa_construct(q, k, v, N, Cq, Ck, want_lse=True)
+    torch.cuda.synchronize()
+    assert none is None
+    for m in (mass, mass2, mass3):
+        assert np.abs(f64(m) - m_ref).max() <= 1e-4
+        assert np.abs(f64(m).sum(3) - 1.0).max() <= 1e-5
+    for x in (lse, lse3):
+        assert np.abs(f64(x)[:, :, :N] - l_ref[:, :, :N]).max() <= 1e-3
+        assert np.all(np.isneginf(f64(x)[:, :, N:]))
+    d_ref, _ = O.dense_attention(qh, kh, vh, N, scale)
+    assert np.abs(f64(o)[:, :, :N] - d_ref[:, :, :N]).max() <= 1e-4
+    assert np.all(f64(o)[:, :, N:] == 0)
+
+    # a support with empty, single-block and full rows, repeated and stray ids
+    rng = np.random.default_rng(800 + CASES.index(case))
+    rows = []
+    for r in range(H * n_q):
+        ids = rng.permutation(n_k)[:[0, 1, n_k, max(1, n_k // 2)][r % 4]]
+        rows.append(np.concatenate([ids, ids[:1], [-1, n_k + 1]]) if r % 3 == 0 else ids)
+    rp = np.concatenate([[0], np.cumsum([len(x) for x in rows])]).astype(np.int32)
+    ci = np.concatenate(rows).astype(np.int32)
+    s, ls = L.losa_sparse_attn_fwd(q, k, v, N, Cq, Ck, torch.from_numpy(rp).cuda(),
+                                   torch.from_numpy(ci).cuda(), want_lse=True)
+    torch.cuda.synchronize()
+    s_ref, ls_ref = O.sparse_attention(qh, kh, vh, N, Cq, Ck, scale, rp, ci)
+    assert np.abs(f64(s)[:, :, :N] - s_ref[:, :, :N]).max() <= 1e-4
+    assert np.all(f64(s)[:, :, N:] == 0)
+    real = np.isfinite(ls_ref[:, :, :N])
+    assert np.array_equal(real, np.isfinite(f64(ls)[:, :, :N]))
+    assert np.abs(f64(ls)[:, :, :N][real] - ls_ref[:, :, :N][real]).max() <= 1e-3
