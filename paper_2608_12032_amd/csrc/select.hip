@@ -1,22 +1,35 @@
 // Shortest-prefix block selection (Sec. 4.1, Eq. (3)) and CSR emission.
 //
 // Three launches:
-//   select_rows  one workgroup per row r = (b*H + h)*n_q + i.  The row's n_k
-//                masses become 64-bit keys  (~bits(m) << 32) | j : masses are
-//                >= 0, so their float bits order like the values and the
-//                complemented bits sort descending; the low word breaks ties
-//                by the smaller block index.  A bitonic sort in LDS, then an
-//                fp64 inclusive scan of the sorted masses; the prefix length
-//                s is the first position whose cumulative mass reaches tau.
-//                tau >= 1 keeps every key block that holds a real key.  In
-//                the fixed-ratio top-k mode (topk > 0; the ablation of Sec. 5,
-//                Table 2) the scan is skipped and s = min(topk, blocks holding
-//                a real key).  The kept blocks are flagged in a per-row byte
-//                mask and s is stored as the row's count.
+//   select_rows  one wave per row r = (b*H + h)*n_q + i, the row's masses in
+//                its registers.  Masses are >= 0, so their float bits order
+//                like the values; the order is decreasing mass, ties by the
+//                smaller block index.  The cut is found without sorting the
+//                row: a search from the highest bit finds the largest pattern
+//                T whose blocks (bits >= T) weigh at least the target, and
+//                once 64 blocks or fewer share T's bits so far, those alone
+//                are put in order.  Blocks that agree in all bits are taken by
+//                index.  The threshold rule weighs a block by its mass, the
+//                fixed-ratio top-k rule (TOPK; the ablation of Sec. 5, Table
+//                2) by 1 with target min(topk, blocks holding a real key).
+//                tau >= 1 keeps every key block that holds a real key, and so
+//                does a row that never reaches tau.  The kept blocks go to a
+//                bit mask per row, their number to the row's count.
 //   scan_counts  one workgroup: exclusive scan of the counts -> row_ptr.
-//   compact_rows one workgroup per row: the flagged block ids, ascending, at
+//   compact_rows one wave per row: the flagged block ids, ascending, at
 //                col_idx[row_ptr[r] ...].
-// Every step is per row or a fixed-order scan: results are deterministic.
+//
+// Sums.  What decides is the sum of integer weights in units of 2^-56 (a mass
+// of 1 and more counts as 1, which reaches every tau): independent of the
+// order and within n_k 2^-56 of the exact sum.  A step of the search first
+// adds fp32 masses and turns to the integers only where that sum is within its
+// rounding error of tau.
+//
+// Bound: the search's compare, select and add per block and step, and reading
+// the masses.  At 22,296 rows of 3,716 masses (331 MB): select_rows 180 us
+// (1.8 TB/s), where a bitonic sort of each row's 4,096 keys in LDS took 2,314
+// us of barrier steps; compact_rows 33 us (110 us from byte flags), scan_counts
+// 7 us (29 us with one row per load).
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -25,179 +38,308 @@ namespace losa {
 namespace {
 
 constexpr int SEL_T = 256;
+constexpr int SEL_ROWS = SEL_T / 64;  // rows per workgroup, one per wave
 
-__device__ __forceinline__ float clean_mass(float m) { return (m > 0.f) ? m : 0.f; }  // NaN -> 0
+__device__ __forceinline__ uint32_t mass_bits(float m) {  // negative and NaN -> 0
+  return m > 0.f ? __float_as_uint(m) : 0u;
+}
 
-template <int NKP>
-__global__ void __launch_bounds__(SEL_T)
-    select_rows_kernel(const float* __restrict__ mass, int n_q, int n_k, int n_kv, int N,
+// A mass in units of 2^-56, truncated: hi in units of 2^-30 and lo < 2^26.
+__device__ __forceinline__ void split_mass(float m, uint32_t* hi, uint32_t* lo) {
+  const float x = m * 0x1p30f;
+  *hi = (uint32_t)x;
+  *lo = (uint32_t)(__builtin_amdgcn_fractf(x) * 0x1p26f);
+}
+__device__ __forceinline__ uint64_t mass_weight(uint32_t bits) {
+  uint32_t hi, lo;
+  split_mass(fminf(__uint_as_float(bits), 1.f), &hi, &lo);
+  return ((uint64_t)hi << 26) + lo;
+}
+
+// Sum over the wave, the same in every lane.
+template <typename T>
+__device__ __forceinline__ T wave_total(T v) {
+  auto bits = [](T x) { return __builtin_bit_cast(int, x); };
+  auto val = [](int x) { return __builtin_bit_cast(T, x); };
+  v += val(__builtin_amdgcn_update_dpp(0, bits(v), 0x128, 0xf, 0xf, false));  // row_ror:8
+  v += val(__builtin_amdgcn_update_dpp(0, bits(v), 0x124, 0xf, 0xf, false));
+  v += val(__builtin_amdgcn_update_dpp(0, bits(v), 0x122, 0xf, 0xf, false));
+  v += val(__builtin_amdgcn_update_dpp(0, bits(v), 0x121, 0xf, 0xf, false));
+  auto r = __builtin_amdgcn_permlane16_swap(bits(v), bits(v), false, false);
+  v = val(r[0]) + val(r[1]);
+  r = __builtin_amdgcn_permlane32_swap(bits(v), bits(v), false, false);
+  return val(r[0]) + val(r[1]);
+}
+
+__device__ __forceinline__ uint64_t read_lane(uint64_t x, int y) {
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, y) |
+         (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), y) << 32;
+}
+__device__ __forceinline__ int bits_below(uint64_t m, int lane) {
+  return __popcll(m & ((1ull << lane) - 1ull));
+}
+
+// The same value, but opaque: the compiler would otherwise keep what one pass
+// over the row's blocks derives from each of them (split masses, ballots) for
+// the next pass, 64 times over, and spill.
+__device__ __forceinline__ uint32_t fresh(uint32_t& x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// Bytes of a row's bit mask: whole 64-bit words, or one byte for fewer than
+// eight blocks (never more than one byte per block).
+__host__ __device__ inline size_t mask_stride(int n_k) {
+  return n_k < 8 ? 1 : (size_t)((n_k + 63) / 64) * 8;
+}
+
+// V: blocks per lane, j = lane + 64 u
+template <int V, bool TOPK>
+__global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 64 ? 1 : (TOPK ? 3 : 4))))
+    select_rows_kernel(const float* __restrict__ mass, int rows, int n_q, int n_k, int n_kv, int N,
                        int block_q, float tau, int topk, int32_t* __restrict__ counts,
-                       uint8_t* __restrict__ flags) {
-  constexpr int PER = NKP / SEL_T > 0 ? NKP / SEL_T : 1;  // sorted slots per thread
-  __shared__ uint64_t key[NKP];
-  __shared__ double tot[SEL_T];
-  __shared__ int s_found;
-  const int t = threadIdx.x;
-  const int r = blockIdx.x;
-  const int i = r % n_q;
-  const float* mrow = mass + (size_t)r * n_k;
-  uint8_t* frow = flags + (size_t)r * n_k;
+                       uint8_t* __restrict__ masks) {
+  __shared__ uint64_t keys[SEL_ROWS][64];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = blockIdx.x * SEL_ROWS + w;
+  if (r >= rows) return;
+  const bool empty = (r % n_q) * block_q >= N;  // a query block made only of padding
+  bool all = empty || (!TOPK && tau >= 1.0f);   // keep the blocks holding a real key (none if empty)
 
-  if (i * block_q >= N) {  // query block made only of padding: empty row
-    for (int j = t; j < n_k; j += SEL_T) frow[j] = 0;
-    if (t == 0) counts[r] = 0;
-    return;
-  }
-  if (topk <= 0 && tau >= 1.0f) {
-    for (int j = t; j < n_k; j += SEL_T) frow[j] = (j < n_kv) ? 1 : 0;
-    if (t == 0) counts[r] = n_kv;
-    return;
-  }
-
-  for (int p = t; p < NKP; p += SEL_T) {
-    if (p < n_k) {
-      const uint32_t bits = __float_as_uint(clean_mass(mrow[p]));
-      key[p] = ((uint64_t)(~bits) << 32) | (uint32_t)p;
-    } else {
-      key[p] = ~0ull;  // sorts after every real block
-    }
-  }
-  __syncthreads();
-
-  // bitonic sort, ascending
-  for (int size = 2; size <= NKP; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int c = t; c < NKP / 2; c += SEL_T) {
-        const int lo = 2 * c - (c & (stride - 1));
-        const int hi = lo + stride;
-        const bool up = ((lo & size) == 0);
-        const uint64_t a = key[lo], b = key[hi];
-        if ((a > b) == up) {
-          key[lo] = b;
-          key[hi] = a;
+  uint32_t bits[V];
+  uint32_t cut = 0;  // kept: bits > cut, or equal and j <= cut_j
+  int cut_j = -1;
+  int kept_n = 0;
+  if (!all) {
+    // (past the row's end the resource reads zero: a branch per load would
+    // wait out each one's latency)
+    const __amdgpu_buffer_rsrc_t mrs = make_rsrc(mass + (size_t)r * n_k, (uint32_t)n_k * 4);
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+      bits[u] = __builtin_amdgcn_raw_buffer_load_b32(mrs, 4 * lane, 256 * u, 0);
+#pragma unroll
+    for (int u = 0; u < V; ++u) bits[u] = mass_bits(__uint_as_float(bits[u]));
+    uint64_t target = TOPK ? (uint64_t)min(topk, n_kv) : mass_weight(__float_as_uint(tau));
+    if (target == 0) target = 1;
+    // weight of the blocks with bits >= c, c > 0 (threshold rule: if it is
+    // below 2; the high parts then add up to less than 2^32)
+    auto weight_from = [&](uint32_t c) -> uint64_t {
+      uint32_t hi = 0, lo = 0;
+#pragma unroll
+      for (int u = 0; u < V; ++u) {
+        if constexpr (TOPK) {
+          hi += bits[u] >= c;
+        } else {
+          uint32_t h, l;
+          const uint32_t b = fresh(bits[u]);
+          split_mass(b >= c ? __uint_as_float(b) : 0.f, &h, &l);
+          hi += h;
+          lo += l;
         }
       }
-      __syncthreads();
+      if constexpr (TOPK) return wave_total(hi);
+      return ((uint64_t)wave_total(hi) << 26) + ((uint64_t)wave_total(lo >> 16) << 16) +
+             wave_total(lo & 0xffffu);
+    };
+    auto reached = [&](uint32_t c) -> bool {
+      if constexpr (!TOPK) {
+        float s = 0.f;
+#pragma unroll
+        for (int u = 0; u < V; ++u) s += bits[u] >= c ? __uint_as_float(bits[u]) : 0.f;
+        const float d = wave_total(s) - tau;
+        // V + 6 additions: within 2^-17 of the sum
+        static_assert(V + 6 <= 1 << 7, "rounding error of the fp32 sum");
+        if (!(fabsf(d) <= tau * 0x1p-17f)) return __builtin_amdgcn_readfirstlane(d > 0.f);
+      }
+      return weight_from(c) >= target;
+    };
+    uint32_t T = 0;
+    int shift = 31;      // T's bits from here up are settled
+    // whether block u of this lane shares them (threshold rule: a block of
+    // mass 0 cannot move the cut; top-k: it can, if there is such a block)
+    auto shares = [&](int u) -> bool {
+      const uint32_t lo = TOPK ? T : max(T, 1u);
+      return fresh(bits[u]) - lo < T + (1u << shift) - lo && (!TOPK || lane < n_k - 64 * u);
+    };
+    int in_play = 0;     // blocks that share them
+    do {
+      const int stop = shift == 31 ? 18 : (shift == 18 ? 9 : 0);
+      while (shift > stop) {
+        --shift;
+        if (reached(T | 1u << shift)) T |= 1u << shift;
+      }
+      if (!TOPK && T == 0 && !reached(1)) {  // the row never reaches tau
+        all = true;
+        break;
+      }
+      in_play = 0;
+#pragma unroll
+      for (int u = 0; u < V; ++u)
+        in_play += __popcll(__ballot(shares(u)));
+    } while (in_play > 64 && shift > 0);
+
+    if (!all) {
+      const uint64_t base = weight_from(T + (1u << shift));  // heavier than those in play
+      int above = 0;
+#pragma unroll
+      for (int u = 0; u < V; ++u) above += __popcll(__ballot(fresh(bits[u]) >= T + (1u << shift)));
+      if (in_play <= 64) {
+        // one block in play per lane; its rank and the weight before it
+        int at = 0;
+        uint32_t id = lane;
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+          const bool mine = shares(u);
+          const uint64_t bal = __ballot(mine);
+          if (mine)
+            keys[w][at + bits_below(bal, lane)] =
+                ((uint64_t)(~bits[u]) << 32) | (64 * u + fresh(id));
+          at += __popcll(bal);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const uint64_t key = keys[w][lane < in_play ? lane : 0];
+        const uint64_t own = TOPK ? 1 : mass_weight(~(uint32_t)(key >> 32));
+        uint64_t before = base;
+        int rank = 0;
+        for (int y = 0; y < in_play; ++y) {
+          const bool heavier = read_lane(key, y) < key;
+          before += heavier ? read_lane(own, y) : 0;
+          rank += heavier;
+        }
+        const int at_cut = __builtin_ctzll(
+            __ballot(lane < in_play && before < target && before + own >= target));
+        const uint64_t cut_key = read_lane(key, at_cut);
+        cut = ~(uint32_t)(cut_key >> 32);
+        cut_j = (int)(uint32_t)cut_key;
+        kept_n = above + __builtin_amdgcn_readlane(rank, at_cut) + 1;
+      } else {
+        // more than 64 blocks of mass T: the first of them by index
+        const uint64_t each = TOPK ? 1 : mass_weight(T);
+        int need = (int)((target - base + each - 1) / each);
+        cut = T;
+        kept_n = above + need;
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+          const uint64_t bal = __ballot(shares(u));
+          const int n = __popcll(bal);
+          if (need > 0 && need <= n)
+            cut_j = 64 * u + __builtin_ctzll(__ballot(((bal >> lane) & 1) != 0 &&
+                                                      bits_below(bal, lane) == need - 1));
+          need -= n;
+        }
+      }
     }
   }
 
-  if (topk > 0) {  // fixed-ratio top-k: the first min(topk, n_kv) of the order
-    const int s = topk < n_kv ? topk : n_kv;
-    for (int p = t; p < n_k; p += SEL_T) {
-      const int j = (int)(uint32_t)key[p];
-      frow[j] = (p < s) ? 1 : 0;
-    }
-    if (t == 0) counts[r] = s;
-    return;
-  }
-
-  // fp64 inclusive scan: thread t owns sorted slots [t*PER, t*PER + PER)
-  double loc[PER];
-  double run = 0.0;
+  uint64_t word = 0;  // lane u: word u of the row's mask
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int p = t * PER + u;
-    double m = 0.0;
-    if (p < NKP && p < n_k) m = (double)__uint_as_float(~(uint32_t)(key[p] >> 32));
-    run += m;
-    loc[u] = run;
+  for (int u = 0; u < V; ++u) {
+    const uint32_t b = all ? 0 : fresh(bits[u]);
+    const bool kept = all ? !empty && lane < n_kv - 64 * u
+                          : lane < n_k - 64 * u &&
+                                (b > cut || (b == cut && lane <= cut_j - 64 * u));
+    const uint64_t bal = __ballot(kept);
+    if (lane == u) word = bal;
   }
-  tot[t] = run;
-  if (t == 0) s_found = 0x7fffffff;
-  __syncthreads();
-  for (int off = 1; off < SEL_T; off <<= 1) {  // Hillis-Steele over thread totals
-    const double add = (t >= off) ? tot[t - off] : 0.0;
-    __syncthreads();
-    tot[t] += add;
-    __syncthreads();
+  uint8_t* mask = masks + (size_t)r * mask_stride(n_k);
+  if (lane < (n_k + 63) / 64) {
+    if (n_k < 8)
+      *mask = (uint8_t)word;
+    else
+      reinterpret_cast<uint64_t*>(mask)[lane] = word;
   }
-  const double base = (t > 0) ? tot[t - 1] : 0.0;
-  // s = 1 + the first sorted position whose cumulative mass reaches tau
-  int first = 0x7fffffff;
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int p = t * PER + u;
-    if (p < n_k && base + loc[u] >= (double)tau && p + 1 < first) first = p + 1;
-  }
-  if (first != 0x7fffffff) atomicMin(&s_found, first);
-  __syncthreads();
-  const int s = s_found;
-  if (s == 0x7fffffff) {  // threshold never reached (masses sum below tau): keep every real block
-    for (int j = t; j < n_k; j += SEL_T) frow[j] = (j < n_kv) ? 1 : 0;
-    if (t == 0) counts[r] = n_kv;
-    return;
-  }
-  for (int p = t; p < n_k; p += SEL_T) {
-    const int j = (int)(uint32_t)key[p];
-    frow[j] = (p < s) ? 1 : 0;
-  }
-  if (t == 0) counts[r] = s;
+  if (lane == 0) counts[r] = all ? (empty ? 0 : n_kv) : kept_n;
 }
 
 constexpr int SCAN_T = 1024;
 
 __global__ void __launch_bounds__(SCAN_T)
     scan_counts_kernel(const int32_t* __restrict__ counts, int rows, int32_t* __restrict__ row_ptr) {
-  __shared__ int32_t tot[SCAN_T];
-  const int t = threadIdx.x;
-  const int per = (rows + SCAN_T - 1) / SCAN_T;
-  const int lo = min(rows, t * per), hi = min(rows, lo + per);
-  int32_t s = 0;
-  for (int r = lo; r < hi; ++r) s += counts[r];
-  tot[t] = s;
-  __syncthreads();
-  for (int off = 1; off < SCAN_T; off <<= 1) {
-    const int32_t add = (t >= off) ? tot[t - off] : 0;
-    __syncthreads();
-    tot[t] += add;
-    __syncthreads();
-  }
-  int32_t run = (t > 0) ? tot[t - 1] : 0;
-  for (int r = lo; r < hi; ++r) {
-    row_ptr[r] = run;
-    run += counts[r];
-  }
-  if (t == SCAN_T - 1) row_ptr[rows] = tot[SCAN_T - 1];
-}
-
-__global__ void __launch_bounds__(SEL_T)
-    compact_rows_kernel(const uint8_t* __restrict__ flags, const int32_t* __restrict__ row_ptr,
-                        int n_k, int32_t* __restrict__ col_idx) {
-  __shared__ int wtot[SEL_T / 64];
-  const int t = threadIdx.x;
-  const int lane = t & 63, w = t >> 6;
-  const int r = blockIdx.x;
-  const uint8_t* frow = flags + (size_t)r * n_k;
-  int out = row_ptr[r];
-  for (int c0 = 0; c0 < n_k; c0 += SEL_T) {
-    const int j = c0 + t;
-    const bool f = (j < n_k) && frow[j];
-    const uint64_t ball = __ballot(f);
-    const int before = __popcll(ball & ((1ull << lane) - 1ull));
-    if (lane == 0) wtot[w] = __popcll(ball);
-    __syncthreads();
-    int woff = 0, all = 0;
-#pragma unroll
-    for (int ww = 0; ww < SEL_T / 64; ++ww) {
-      woff += (ww < w) ? wtot[ww] : 0;
-      all += wtot[ww];
+  __shared__ int32_t wtot[2][SCAN_T / 64];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+  int32_t run = 0;
+  int par = 0;
+  for (int64_t r0 = 0; r0 < rows; r0 += 4 * SCAN_T, par ^= 1) {
+    const int64_t r = r0 + 4 * t;  // four consecutive rows per thread
+    i32x4 c = i32x4{};
+    if (r + 4 <= rows) {
+      c = *reinterpret_cast<const i32x4*>(counts + r);
+    } else {
+      for (int e = 0; e < 4; ++e)
+        if (r + e < rows) c[e] = counts[r + e];
     }
-    if (f) col_idx[out + woff + before] = j;
-    out += all;
+    const int32_t own = c[0] + c[1] + c[2] + c[3];
+    int32_t incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int32_t y = __shfl_up(incl, o);
+      incl += lane >= o ? y : 0;
+    }
+    if (lane == 63) wtot[par][w] = incl;
     __syncthreads();
+    int32_t before = 0, total = 0;
+#pragma unroll
+    for (int y = 0; y < SCAN_T / 64; ++y) {
+      before += y < w ? wtot[par][y] : 0;
+      total += wtot[par][y];
+    }
+    int32_t at = run + before + incl - own;
+    i32x4 o4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o4[e] = at;
+      at += c[e];
+    }
+    if (r + 4 <= rows) {
+      *reinterpret_cast<i32x4*>(row_ptr + r) = o4;
+    } else {
+      for (int e = 0; e < 4; ++e)
+        if (r + e < rows) row_ptr[r + e] = o4[e];
+    }
+    run += total;
+  }
+  if (t == 0) row_ptr[rows] = run;
+}
+
+// One wave per row: lane w holds word w of the row's mask (n_k <= 4,096), and
+// each word's ids leave in one contiguous store.
+__global__ void __launch_bounds__(SEL_T)
+    compact_rows_kernel(const uint8_t* __restrict__ masks, const int32_t* __restrict__ row_ptr,
+                        int rows, int n_k, int32_t* __restrict__ col_idx) {
+  const int lane = threadIdx.x & 63;
+  const int r = blockIdx.x * SEL_ROWS + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (r >= rows) return;
+  const int words = (n_k + 63) / 64;
+  const uint8_t* mrow = masks + (size_t)r * mask_stride(n_k);
+  uint64_t mine = 0;
+  if (lane < words) mine = n_k < 8 ? *mrow : reinterpret_cast<const uint64_t*>(mrow)[lane];
+  int32_t* out = col_idx + row_ptr[r];
+  for (int w = 0; w < words; ++w) {
+    const uint64_t m = read_lane(mine, w);
+    if ((m >> lane) & 1) out[bits_below(m, lane)] = w * 64 + lane;
+    out += __popcll(m);
   }
 }
 
-template <int NKP>
+template <int V>
 void launch_sel(const float* mass, int rows, int n_q, int n_k, int n_kv, int N, int block_q,
-                float tau, int topk, int32_t* counts, uint8_t* flags, hipStream_t stream) {
-  hipLaunchKernelGGL(select_rows_kernel<NKP>, dim3(rows), dim3(SEL_T), 0, stream, mass, n_q, n_k,
-                     n_kv, N, block_q, tau, topk, counts, flags);
+                float tau, int topk, int32_t* counts, uint8_t* masks, hipStream_t stream) {
+  const dim3 grid((rows + SEL_ROWS - 1) / SEL_ROWS);
+  if (topk > 0)
+    hipLaunchKernelGGL((select_rows_kernel<V, true>), grid, dim3(SEL_T), 0, stream, mass, rows,
+                       n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks);
+  else
+    hipLaunchKernelGGL((select_rows_kernel<V, false>), grid, dim3(SEL_T), 0, stream, mass, rows,
+                       n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks);
 }
 
 }  // namespace
 
 size_t select_workspace_bytes(int rows, int n_k) {
+  // row counts, then one byte per block (the bit masks take an eighth of it)
   const size_t counts = ((size_t)rows * 4 + 255) & ~(size_t)255;
   return counts + (size_t)rows * n_k;
 }
@@ -212,20 +354,20 @@ hipError_t launch_select(const float* mass, int B, int H, int N, int block_q, in
   const int n_kv = (N + block_k - 1) / block_k;
   const int rows = B * H * n_q;
   int32_t* counts = static_cast<int32_t*>(workspace);
-  uint8_t* flags =
+  uint8_t* masks =
       static_cast<uint8_t*>(workspace) + (((size_t)rows * 4 + 255) & ~(size_t)255);
-  if (n_k <= 64) launch_sel<64>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, flags, stream);
-  else if (n_k <= 256) launch_sel<256>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, flags, stream);
-  else if (n_k <= 1024) launch_sel<1024>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, flags, stream);
-  else if (n_k <= 4096) launch_sel<4096>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, flags, stream);
+  if (n_k <= 64) launch_sel<1>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks, stream);
+  else if (n_k <= 256) launch_sel<4>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks, stream);
+  else if (n_k <= 1024) launch_sel<16>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks, stream);
+  else if (n_k <= 4096) launch_sel<64>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks, stream);
   else return hipErrorInvalidValue;
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(SCAN_T), 0, stream, counts, rows, row_ptr);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(compact_rows_kernel, dim3(rows), dim3(SEL_T), 0, stream, flags, row_ptr, n_k,
-                     col_idx);
+  hipLaunchKernelGGL(compact_rows_kernel, dim3((rows + SEL_ROWS - 1) / SEL_ROWS),
+                     dim3(SEL_T), 0, stream, masks, row_ptr, rows, n_k, col_idx);
   return hipGetLastError();
 }
 
