@@ -305,9 +305,9 @@ constexpr int fwd_waves_per_simd() {
   return BLK == 128 ? (D == 64 ? 3 : 2) : 1;
 }
 
-template <int D, int BLK, int BK, bool DENSE>
-__global__ void __launch_bounds__(BLK * 2)
-    __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<D, BLK>())))
+template <int D, int BLK, int BK, bool DENSE, int KSP>
+__global__ void __launch_bounds__(BLK * 2 * KSP)
+    __attribute__((amdgpu_waves_per_eu(KSP == 1 ? fwd_waves_per_simd<D, BLK>() : BLK / 64)))
     sparse_fwd_bf16_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K,
                            const __bf16* __restrict__ Vt, const int32_t* __restrict__ row_ptr,
                            const int32_t* __restrict__ col_idx, int64_t col_len,
@@ -318,13 +318,17 @@ __global__ void __launch_bounds__(BLK * 2)
   constexpr int NS = C::NS;
   constexpr int R = C::R;
   constexpr int BPI = C::BPI;
-  // K ring at smem, V^T ring at smem + RING; slot x at + x*SUB
-  __shared__ __attribute__((aligned(1024))) char smem[2 * C::RING];
+  constexpr int NT = C::NT * KSP;
+  constexpr int NWV = C::NW * KSP;
+  // per key split: K ring at smem, V^T ring at smem + RING; slot x at + x*SUB
+  __shared__ __attribute__((aligned(1024))) char smem[KSP * 2 * C::RING];
   __shared__ uint16_t list[kMaxList];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int w = KSP == 1 ? wv : wv % C::NW;   // 32-row group
+  const int sp = KSP == 1 ? 0 : wv / C::NW;   // key split
   const int l32 = lane & 31;
   const int g = lane >> 5;
 
@@ -332,61 +336,14 @@ __global__ void __launch_bounds__(BLK * 2)
   // attention of the construction step); rows run in id order, each XCD on a
   // contiguous range of them.  A template flag, so that the two modes are
   // separate kernels in a trace.
-  const int r = DENSE ? xcd_remap(blockIdx.x, gridDim.x) : order[blockIdx.x];
+  // Sparse calls without an order run in id order too.
+  const int r = DENSE || order == nullptr ? xcd_remap(blockIdx.x, gridDim.x) : order[blockIdx.x];
   const int bh = r / n_q;
   const int qb = r - bh * n_q;
   const size_t head = (size_t)bh * n_pad * D;
   const uint32_t head_bytes = (uint32_t)((size_t)n_pad * D * 2);
   const i32x4_t krs = rsrc_words(K + head, head_bytes);
   const i32x4_t vrs = rsrc_words(Vt + head, head_bytes);
-
-  // ---- the row's distinct valid key blocks, ascending ---------------------
-  // (flags and per-wave counts live in the rings, unused until the first load)
-  int nb = 0;
-  if constexpr (DENSE) {
-    nb = (N + BK - 1) / BK;
-    for (int j = tid; j < nb; j += C::NT) list[j] = (uint16_t)j;
-    __syncthreads();
-  } else {
-    uint8_t* const flag = reinterpret_cast<uint8_t*>(smem);
-    int* const wcount = reinterpret_cast<int*>(smem + kMaxList);
-    for (int j = tid; j < n_k; j += C::NT) flag[j] = 0;
-    __syncthreads();
-    int64_t e0 = row_ptr[r], e1 = row_ptr[r + 1];
-    e0 = e0 < 0 ? 0 : (e0 > col_len ? col_len : e0);
-    e1 = e1 < e0 ? e0 : (e1 > col_len ? col_len : e1);
-    for (int64_t e = e0 + tid; e < e1; e += C::NT) {
-      const int j = col_idx[e];
-      if (j >= 0 && j < n_k) flag[j] = 1;
-    }
-    __syncthreads();
-    for (int c0 = 0; c0 < n_k; c0 += C::NT) {
-      const int j = c0 + tid;
-      const bool f = (j < n_k) && flag[j] != 0;
-      const uint64_t bal = __ballot(f);
-      const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
-                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
-      if (lane == 0) wcount[w] = __popcll(bal);
-      __syncthreads();
-      int before = 0, total = 0;
-#pragma unroll
-      for (int x = 0; x < C::NW; ++x) {
-        const int c = wcount[x];
-        before += (x < w) ? c : 0;
-        total += c;
-      }
-      if (f) list[nb + before + below] = (uint16_t)j;
-      nb += total;
-      __syncthreads();
-    }
-    nb = __builtin_amdgcn_readfirstlane(nb);
-  }
-  // sub-tiles in the stream.  With 32-key blocks (one sub-tile each) the
-  // stream is padded to whole loop passes with sub-tiles whose keys are all
-  // masked (they add nothing to O or l); larger blocks fill passes exactly,
-  // or leave half a pass that the loop stops after.
-  const int S_real = nb * NS;
-  const int S = (NS == 1) ? (S_real + R - 1) / R * R : S_real;
 
   // this lane's query row and its Q^T operand (8 bf16 per k-step).  Padding
   // rows take Q = 0, so their scores stay finite whatever the padding holds
@@ -399,9 +356,62 @@ __global__ void __launch_bounds__(BLK * 2)
 #pragma unroll
     for (int st = 0; st < C::KS; ++st) qreg[st] = qvalid ? qp[2 * st + g] : bf16x8_t{};
   }
+
+  // ---- the row's distinct valid key blocks, ascending ---------------------
+  // (flags and per-wave counts live in the rings, unused until the first load)
+  int nb = 0;
+  if constexpr (DENSE) {
+    nb = (N + BK - 1) / BK;
+    for (int j = tid; j < nb; j += NT) list[j] = (uint16_t)j;
+    __syncthreads();
+  } else {
+    uint8_t* const flag = reinterpret_cast<uint8_t*>(smem);
+    int* const wcount = reinterpret_cast<int*>(smem + kMaxList);
+    for (int j = tid; j < n_k; j += NT) flag[j] = 0;
+    __syncthreads();
+    int64_t e0 = row_ptr[r], e1 = row_ptr[r + 1];
+    e0 = e0 < 0 ? 0 : (e0 > col_len ? col_len : e0);
+    e1 = e1 < e0 ? e0 : (e1 > col_len ? col_len : e1);
+    for (int64_t e = e0 + tid; e < e1; e += NT) {
+      const int j = col_idx[e];
+      if (j >= 0 && j < n_k) flag[j] = 1;
+    }
+    __syncthreads();
+    for (int c0 = 0; c0 < n_k; c0 += NT) {
+      const int j = c0 + tid;
+      const bool f = (j < n_k) && flag[j] != 0;
+      const uint64_t bal = __ballot(f);
+      const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
+      if (lane == 0) wcount[wv] = __popcll(bal);
+      __syncthreads();
+      int before = 0, total = 0;
+#pragma unroll
+      for (int x = 0; x < NWV; ++x) {
+        const int c = wcount[x];
+        before += (x < wv) ? c : 0;
+        total += c;
+      }
+      if (f) list[nb + before + below] = (uint16_t)j;
+      nb += total;
+      __syncthreads();
+    }
+    nb = __builtin_amdgcn_readfirstlane(nb);
+  }
+  // sub-tiles in the stream.  With 32-key blocks (one sub-tile each) the
+  // stream is padded to whole loop passes with sub-tiles whose keys are all
+  // masked (they add nothing to O or l); larger blocks fill passes exactly,
+  // or leave half a pass that the loop stops after.
+  // A key split takes its half of the list; both run the trips of the longer.
+  const int nb_trip = KSP == 1 ? nb : (nb + KSP - 1) / KSP;
+  const int nb0 = sp * nb_trip;
+  const int S_real = KSP == 1 ? nb * NS : max(0, min(nb_trip, nb - nb0)) * NS;
+  const int S = (NS == 1) ? (nb_trip + R - 1) / R * R : nb_trip * NS;
+
   // per-lane LDS addresses of the operand reads in K slot 0 / V^T slot 0; the
   // slot and the d sub-block are immediates
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  char* const ring = smem + sp * 2 * C::RING;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
   uint32_t ka[C::KS], va[2];
 #pragma unroll
   for (int st = 0; st < C::KS; ++st)
@@ -437,7 +447,7 @@ __global__ void __launch_bounds__(BLK * 2)
   };
   // list entry x as a scalar, clamped into the list
   auto block_at = [&](int x) -> int {
-    return __builtin_amdgcn_readfirstlane((int)list[x < nb ? x : nb - 1]);
+    return __builtin_amdgcn_readfirstlane((int)list[nb0 + x < nb ? nb0 + x : nb - 1]);
   };
 
   f32x16_t oacc[C::DB];
@@ -466,8 +476,8 @@ __global__ void __launch_bounds__(BLK * 2)
       load_k(y, jy, y % NS);
       if (y < R - 2) load_v(y, jy, y % NS);
     }
-    for (int x = tid * 16; x < C::SUB; x += C::NT * 16)
-      *reinterpret_cast<f32x4_t*>(smem + C::RING + (R - 1) * C::SUB + x) = f32x4_t{};
+    for (int x = (w * 64 + lane) * 16; x < C::SUB; x += C::NT * 16)
+      *reinterpret_cast<f32x4_t*>(ring + C::RING + (R - 1) * C::SUB + x) = f32x4_t{};
 #pragma unroll
     for (int a2 = 0; a2 < 2; ++a2)
 #pragma unroll
@@ -566,7 +576,7 @@ __global__ void __launch_bounds__(BLK * 2)
       int jf[BPI];
 #pragma unroll
       for (int x = 0; x < BPI; ++x) {
-        const int xi = (u + 2) * BPI + x;
+        const int xi = nb0 + (u + 2) * BPI + x;
         jf[x] = (int)list[xi < nb ? xi : nb - 1];
       }
       sub_iter(I0{}, u);
@@ -594,8 +604,42 @@ __global__ void __launch_bounds__(BLK * 2)
                                    pb[1], oacc);
   }
 
+  float l_tot = add_partner(l_run);
+  if constexpr (KSP == 2) {
+    // the second half's state goes through LDS (the rings are done with) and
+    // the first half's waves merge it: common max, sums and outputs rescaled
+    f32x4_t* const po = reinterpret_cast<f32x4_t*>(smem) + w * (C::DB * 4 * 64) + lane;
+    float* const ml = reinterpret_cast<float*>(smem + C::NW * C::DB * 4096) + w * 128 + lane;
+    static_assert(C::NW * (C::DB * 4096 + 512) <= KSP * 2 * C::RING, "states fit the rings");
+    __syncthreads();
+    if (sp == 1) {
+      ml[0] = m_run;
+      ml[64] = l_tot;
+#pragma unroll
+      for (int db = 0; db < C::DB; ++db)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          po[(db * 4 + e) * 64] = f32x4_t{oacc[db][4 * e], oacc[db][4 * e + 1],
+                                          oacc[db][4 * e + 2], oacc[db][4 * e + 3]};
+    }
+    __syncthreads();
+    if (sp == 1) return;
+    const float m1 = ml[0];
+    const float m_new = fmaxf(m_run, m1);
+    const float a0 = fast_exp2(m_run - m_new), a1 = fast_exp2(m1 - m_new);
+    m_run = m_new;
+    l_tot = l_tot * a0 + ml[64] * a1;
+#pragma unroll
+    for (int db = 0; db < C::DB; ++db)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const f32x4_t p = po[(db * 4 + e) * 64];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) oacc[db][4 * e + u] = oacc[db][4 * e + u] * a0 + p[u] * a1;
+      }
+  }
+
   // ---- epilogue: O = O^T / l, lse -----------------------------------------
-  const float l_tot = add_partner(l_run);
   const bool row_ok = (qrow < N) && (l_tot > 0.f);
   const float inv = row_ok ? 1.0f / l_tot : 0.f;
   __bf16* orow = O + head + (size_t)qrow * D;
@@ -701,7 +745,19 @@ __global__ void __launch_bounds__(256)
 // per row) at the next 256-byte boundary.
 size_t vt_bytes(int BH, int n_pad, int d) { return ((size_t)BH * n_pad * d * 2 + 255) / 256 * 256; }
 
-template <int D, int BLK, int BK>
+// Two key splits per row where a call's rows leave CUs with one workgroup or
+// none: a wave alone on its SIMD waits out its own exponentials and barriers.
+// Full rows, one split against two: 256 rows 91.0 / 81.5 us (d = 128, 128-row
+// blocks), 59.2 / 48.6 (d = 64), 42.2 / 29.8 (d = 128, 64-row blocks); 320 rows
+// 136.8 / 152.6, 89.6 / 97.7, 54.4 / 57.2.  With 64-row blocks at d = 64 two
+// split workgroups fit a CU: 79.8 / 54.1 at 512 rows, 103 / 92 at 640 (59 / 60
+// with half the blocks kept).  Under 512 keys the merge costs more than half
+// the stream: 12.9 / 14.4 us at 128 keys.
+inline bool split_keys(int d, int blk, int64_t rows, int n_pad) {
+  return rows <= (d == 64 && blk == 64 ? 512 : 256) && n_pad >= 512;
+}
+
+template <int D, int BLK, int BK, int KSP>
 hipError_t launch_fwd(const void* q, const void* k, const void* v, int B, int H, int N, int n_pad,
                       float scale, const int32_t* row_ptr, const int32_t* col_idx,
                       int64_t col_len, void* o, float* lse, void* workspace, hipStream_t stream) {
@@ -711,14 +767,18 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, int B, int H,
   const int rows = BH * n_q;
   __bf16* vt = static_cast<__bf16*>(workspace);
   int* order = reinterpret_cast<int*>(static_cast<char*>(workspace) + vt_bytes(BH, n_pad, D));
-  const int per_xcd = (rows + 7) / 8;
-  hipLaunchKernelGGL(order_rows_kernel, dim3((per_xcd + kOrderChunk - 1) / kOrderChunk, 8),
-                     dim3(kOrderChunk), 0, stream, row_ptr, col_len, rows, n_k, order);
+  if (KSP > 1) {
+    order = nullptr;  // every row starts at once
+  } else {
+    const int per_xcd = (rows + 7) / 8;
+    hipLaunchKernelGGL(order_rows_kernel, dim3((per_xcd + kOrderChunk - 1) / kOrderChunk, 8),
+                       dim3(kOrderChunk), 0, stream, row_ptr, col_len, rows, n_k, order);
+  }
   dim3 tgrid(n_pad / 64, BH);
   hipLaunchKernelGGL(transpose_v_kernel<D>, tgrid, dim3(256), 0, stream,
                      static_cast<const __bf16*>(v), vt, n_pad);
-  hipLaunchKernelGGL((sparse_fwd_bf16_kernel<D, BLK, BK, false>), dim3(rows),
-                     dim3(FwdCfg<D, BLK, BK>::NT), 0, stream, static_cast<const __bf16*>(q),
+  hipLaunchKernelGGL((sparse_fwd_bf16_kernel<D, BLK, BK, false, KSP>), dim3(rows),
+                     dim3(FwdCfg<D, BLK, BK>::NT * KSP), 0, stream, static_cast<const __bf16*>(q),
                      static_cast<const __bf16*>(k), static_cast<const __bf16*>(vt), row_ptr,
                      col_idx, col_len, static_cast<__bf16*>(o), lse, nullptr, order, n_q, n_k, N,
                      n_pad, scale * kLog2e);
@@ -728,7 +788,7 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, int B, int H,
 // Dense attention of every query block over every valid key (the forward
 // kernel with full rows): O, lse and, if stat is given, the block statistics
 // of the construction step.
-template <int D, int BLK, int BK>
+template <int D, int BLK, int BK, int KSP>
 hipError_t launch_dense(const void* q, const void* k, const void* v, int B, int H, int N,
                         int n_pad, float scale, void* o, float* lse, float* stat, void* workspace,
                         hipStream_t stream) {
@@ -740,8 +800,8 @@ hipError_t launch_dense(const void* q, const void* k, const void* v, int B, int 
   dim3 tgrid(n_pad / 64, BH);
   hipLaunchKernelGGL(transpose_v_kernel<D>, tgrid, dim3(256), 0, stream,
                      static_cast<const __bf16*>(v), vt, n_pad);
-  hipLaunchKernelGGL((sparse_fwd_bf16_kernel<D, BLK, BK, true>), dim3(rows),
-                     dim3(FwdCfg<D, BLK, BK>::NT), 0, stream, static_cast<const __bf16*>(q),
+  hipLaunchKernelGGL((sparse_fwd_bf16_kernel<D, BLK, BK, true, KSP>), dim3(rows),
+                     dim3(FwdCfg<D, BLK, BK>::NT * KSP), 0, stream, static_cast<const __bf16*>(q),
                      static_cast<const __bf16*>(k), static_cast<const __bf16*>(vt), nullptr,
                      nullptr, 0, static_cast<__bf16*>(o), lse, stat, nullptr, n_q, n_k, N, n_pad,
                      scale * kLog2e);
@@ -755,10 +815,13 @@ hipError_t launch_sparse_fwd_bf16(int d, int blk, int blk_k, const void* q, cons
                                   const int32_t* row_ptr, const int32_t* col_idx,
                                   int64_t col_len, void* o, float* lse, void* workspace,
                                   hipStream_t stream) {
+  const bool split = split_keys(d, blk, (int64_t)B * H * (n_pad / blk), n_pad);
 #define LOSA_FWD(DD, BB, KK)                                                                 \
   if (d == DD && blk == BB && blk_k == KK)                                                   \
-    return launch_fwd<DD, BB, KK>(q, k, v, B, H, N, n_pad, scale, row_ptr, col_idx, col_len, \
-                                  o, lse, workspace, stream);
+    return split ? launch_fwd<DD, BB, KK, 2>(q, k, v, B, H, N, n_pad, scale, row_ptr, col_idx, \
+                                             col_len, o, lse, workspace, stream)             \
+                 : launch_fwd<DD, BB, KK, 1>(q, k, v, B, H, N, n_pad, scale, row_ptr, col_idx, \
+                                             col_len, o, lse, workspace, stream);
   LOSA_FWD(128, 128, 128)
   LOSA_FWD(64, 128, 128)
   LOSA_FWD(128, 64, 64)
@@ -773,11 +836,17 @@ hipError_t launch_sparse_fwd_bf16(int d, int blk, int blk_k, const void* q, cons
 
 hipError_t launch_dense_bf16(int d, int blk, int blk_k, const void* q, const void* k,
                              const void* v, int B, int H, int N, int n_pad, float scale, void* o,
-                             float* lse, float* stat, void* workspace, hipStream_t stream) {
+                             float* lse, float* stat, void* workspace, int64_t call_rows,
+                             hipStream_t stream) {
+  // by the whole call's rows: its groups of heads, and the sparse forward over
+  // the same shape, then split alike and give the same bits
+  const bool split = split_keys(d, blk, call_rows, n_pad);
 #define LOSA_DENSE(DD, BB, KK)                                                                \
   if (d == DD && blk == BB && blk_k == KK)                                                    \
-    return launch_dense<DD, BB, KK>(q, k, v, B, H, N, n_pad, scale, o, lse, stat, workspace, \
-                                    stream);
+    return split ? launch_dense<DD, BB, KK, 2>(q, k, v, B, H, N, n_pad, scale, o, lse, stat,  \
+                                               workspace, stream)                             \
+                 : launch_dense<DD, BB, KK, 1>(q, k, v, B, H, N, n_pad, scale, o, lse, stat,  \
+                                               workspace, stream);
   LOSA_DENSE(128, 128, 128)
   LOSA_DENSE(64, 128, 128)
   LOSA_DENSE(128, 64, 64)
