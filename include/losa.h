@@ -112,11 +112,12 @@ losa_status losa_calibrate_mass(const void* q, const void* k, losa_dtype dtype, 
  *
  * For each row r: order the row's key blocks by decreasing mass, ties by the
  * smaller block index (the paper leaves ties arbitrary); keep the shortest
- * prefix whose cumulative mass (summed in integer units of 2^-56, so
- * exact to n_k 2^-56) reaches tau (the exact fp32 value passed).  tau >= 1 keeps every key block that holds a valid key, so
- * the sparse forward then equals dense attention.  A row whose masses never
- * reach tau also keeps every such block.  Rows of query blocks with no valid
- * query are empty.  Masses that are negative or NaN count as 0.
+ * prefix whose cumulative mass (summed in integer units of 2^-56, so exact to
+ * n_k 2^-56) reaches tau (the exact fp32 value passed).  tau >= 1 keeps every
+ * key block that holds a valid key, so the sparse forward then equals dense
+ * attention.  A row whose masses never reach tau also keeps every such block.
+ * Rows of query blocks with no valid query are empty.  Masses that are
+ * negative or NaN count as 0.
  *
  * mass              fp32 [B][H][n_q][n_k] (e.g. from losa_calibrate_mass).
  * row_ptr           out, int32 [B*H*n_q + 1]: row_ptr[0] = 0, row_ptr[end] = nnz.
@@ -195,7 +196,7 @@ losa_status losa_block_recall(const float* mass, int B, int H, int N, int block_
  * lse         out, nullable, fp32 [B][H][N_pad]: natural-log logsumexp over
  *             K(q) of the scaled scores; -inf for empty or padding rows.
  * workspace   >= losa_workspace_bytes(2, ...) bytes, rewritten by every call
- *             (bf16: a transposed copy of V in the kernel's tile layout,
+ *             (bf16: room for a copy of V, made only where o overlaps v,
  *             B*H*N_pad*d*2 bytes rounded up to 256, then the rows' dispatch
  *             order, 4*B*H*n_q bytes; f32: none).
  * Arithmetic (bf16): Q K^T and P V on bf16 matrix cores with fp32
@@ -214,7 +215,7 @@ losa_status losa_sparse_attn_fwd(const void* q, const void* k, const void* v, lo
  * running under HIP graph capture that may not call hipMalloc, tight serving
  * loops, harnesses that forbid allocation.  Same arguments, results and
  * kernels as losa_sparse_attn_fwd (bitwise the same output), without the
- * workspace: the bf16 forward's scratch (the transposed copy of V and the
+ * workspace: the bf16 forward's scratch (room for a copy of V and the
  * rows' dispatch order, B*H*N_pad*d*2 bytes rounded up to 256 plus 4*B*H*n_q
  * bytes) lives in a device array the library holds, LOSA_NOALLOC_SCRATCH_BYTES
  * per GPU, reserved on each GPU the library runs on until the process ends.

@@ -87,14 +87,14 @@ constexpr size_t kMaxLds = 160 * 1024;
 
 // Workspace of the one-sweep bf16 calibration and of the bf16 construction
 // step for a group of G heads: the block statistics, the heads' lse, then
-// (construction only) the dense forward's V^T.  Heads are processed G at a
+// (construction only) the dense forward's workspace.  Heads are processed G at a
 // time; G follows from the bytes the caller gives.
 constexpr size_t kStatGroupCap = (size_t)16 << 30;  // suggested size: up to 16 GiB of groups
 
 size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct StatLayout {
-  size_t lse, fwd, total;  // byte offsets of lse and V^T (statistics at 0), total size
+  size_t lse, fwd, total;  // byte offsets of lse and the forward's workspace, total size
 };
 
 StatLayout stat_layout(const Shape& s, int G, bool with_fwd) {

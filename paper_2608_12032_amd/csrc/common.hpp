@@ -118,6 +118,13 @@ __device__ __forceinline__ float add_partner(float x) {
 
 typedef __attribute__((address_space(3))) const bf16x8_t lds_bf16x8_t;
 
+// Transposing 8-byte LDS read: within a 16-lane group, lane 4a+b gets element b
+// of the 8 bytes addressed by lanes 4e+a, e = 0..3.
+__device__ __forceinline__ bf16x4_t lds_read_tr8(uint32_t addr) {
+  typedef __attribute__((address_space(3))) bf16x4_t lds_bf16x4_t;
+  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16(reinterpret_cast<lds_bf16x4_t*>(addr));
+}
+
 // 16-byte LDS read at byte address `addr` (+ a compile-time immediate).
 __device__ __forceinline__ bf16x8_t lds_read16(uint32_t addr) {
   return *reinterpret_cast<lds_bf16x8_t*>(addr);

@@ -9,8 +9,8 @@
 // receive the device address the lookup returns, never the name.
 //
 // Calls on one GPU share that GPU's copy and leave the last call's contents in
-// it.  The forward rewrites everything it reads from the scratch (V^T and the
-// dispatch order) before reading it, so nothing needs to start at zero, but
+// it.  The forward rewrites everything it reads from the scratch (the
+// dispatch order, a copy of V) before reading it, so nothing needs to start at zero, but
 // two calls that overlap in time on one GPU (different streams, or different
 // host threads without ordering) race on it.
 #include <hip/hip_runtime.h>

@@ -25,18 +25,20 @@
 // (lanes 32g..32g+31) holds, in register element e, the key
 //   16*step + 4*g + e + (e >= 4 ? 4 : 0),
 // which is where the S^T accumulator put it.  The A operand V^T must hold the
-// same key in the same (lane group, element) slot; the transposed copy of V
-// therefore stores, within every group of 16 keys, positions 4..7 and 8..11
-// swapped (an involution), so each lane's 8 keys are 16 contiguous bytes.
+// same key in the same (lane group, element) slot, for the lane's d row.  V
+// stays row-major in LDS: ds_read_b64_tr_b16 hands lane 4a+b of a 16-lane group
+// element b of the 8 bytes that lanes 4e+a, e = 0..3, address, so with lane
+// 4e+a at (key 4x+e, d 4a..4a+3) each lane gets four consecutive keys of its d
+// row, and two such reads make an operand.
 //
 // Streaming.  The row's keys are a stream of 32-key sub-tiles (NS = BK/32 per
 // key block of BK keys; with BK = 32 the stream is padded to whole loop passes
-// with sub-tiles whose keys are all masked).  K and V^T sub-tiles pass through
+// with sub-tiles whose keys are all masked).  K and V sub-tiles pass through
 // two rings of kRing LDS slots, filled by 16-byte buffer loads that write LDS
 // directly.  Sub-iteration s
-// reads K sub-tile s+1 (scores of the next sub-tile) and V^T sub-tile s-1
+// reads K sub-tile s+1 (scores of the next sub-tile) and V sub-tile s-1
 // (P V of the previous one); after the barrier that opens it, the slots that
-// sub-iteration s-1 finished with are refilled with K sub-tile s+kRing and V^T
+// sub-iteration s-1 finished with are refilled with K sub-tile s+kRing and V
 // sub-tile s+kRing-2, both needed kRing-1 sub-iterations later.  Every
 // sub-iteration issues the same number of loads (past the end of the stream
 // they fetch the last block again), so one fixed vmcnt wait before each
@@ -47,10 +49,19 @@
 // sched_group_barrier.
 //
 // LDS images.  A K sub-tile is 32 rows of D bf16, row-major, 16-byte chunks
-// XOR-swizzled by 256-byte line; V^T is kept in global memory already in the
-// LDS image of its sub-tiles (written by the transpose kernel), so its loads
-// are plain contiguous copies.  Both swizzles make the 16 rows read by one
-// 16-lane group of an operand read land in distinct banks.
+// XOR-swizzled by 256-byte line, so that the 16 rows read by one 16-lane group
+// land in distinct banks.  A V sub-tile is eight pieces of 4 keys, each the
+// keys' 64-byte slices of d block 0, then of block 1, ...: a transposing read
+// takes 256 contiguous bytes per 32 lanes (no bank twice), and key step, half
+// and d block are all immediates of one base address.  The direct loads write
+// LDS linearly, so both images are made by the lanes' global addresses.
+//
+// V straight from its row-major tensor replaced a transposed copy made by a
+// kernel of its own before each call (33 us at 12 heads x 32,768 x 128).  The
+// forward itself pays 0.6 to 1.4 % for twice the V read instructions: whole
+// calls 2,962 -> 2,949 us (Wan shape), 2,904 -> 2,863 (32-key blocks), 3,132 ->
+// 3,108 (CogVideoX), 291 -> 260 (Wan, 2.7 % of the blocks), 33.6 -> 28.4 (1,560
+// tokens); HunyuanVideo 64.6 -> 64.8 ms.
 //
 // Softmax.  Probabilities are taken against the running max without looking
 // at the sub-tile's scores first; only when a lane's sub-tile sum exceeds
@@ -85,13 +96,6 @@ constexpr int kMaxList = kSparseFwdMaxNk;
 // Sub-tile slots per operand ring.
 constexpr int kRing = 4;
 
-// Position <-> key permutation inside a group of 16 keys (swap of quads 1, 2).
-__device__ __forceinline__ int perm16(int p) {
-  const int quad = p >> 2;
-  const int q2 = (quad == 1) ? 2 : (quad == 2 ? 1 : quad);
-  return (q2 << 2) | (p & 3);
-}
-
 template <int D, int BLK, int BK>
 struct FwdCfg {
   static constexpr int NW = BLK / 32;                // waves per workgroup
@@ -100,15 +104,15 @@ struct FwdCfg {
   static constexpr int DB = D / 32;                  // 32-row d sub-blocks of O^T
   static constexpr int NS = BK / 32;                 // 32-key sub-tiles per key block
   static constexpr int R = kRing;                    // slots per ring
-  static constexpr int LEAD = D == 64 ? 6 : 4;       // MFMAs an LDS operand read leads by
+  static constexpr int LEAD = D == 64 ? 4 : 2;       // MFMAs an LDS operand read leads by
   static constexpr int BPI = R / NS;                 // key blocks per unrolled loop pass
-  static constexpr int SUB = 32 * D * 2;             // bytes of a K or V^T sub-tile
+  static constexpr int SUB = 32 * D * 2;             // bytes of a K or V sub-tile
   static constexpr int RING = R * SUB;               // bytes of one ring
   static constexpr int LPW = SUB / (1024 * NW);      // 1 KiB wave loads per sub-tile
   static constexpr int KROW = D * 2;                 // bytes of a K row
   static constexpr int KCPR = KROW / 16;             // 16-byte chunks per K row
   static constexpr int KRPL = 256 / KROW;            // K rows per 256-byte line
-  static constexpr int VDB = 32 * 64;                // bytes of 32 V^T rows in a sub-tile
+  static constexpr int VPC = 8 * D;                  // bytes of a 4-key piece of a V sub-tile
   static_assert(SUB % (1024 * NW) == 0, "sub-tile must split into whole wave loads");
   static_assert(R % NS == 0 && R >= 4 && (R & 1) == 0, "ring holds whole key blocks");
   static_assert(KS == 2 * DB, "QK and PV steps alternate one to one");
@@ -127,13 +131,23 @@ __device__ __forceinline__ int kswz(int row, int c) {
 // precomputed address per (slot, k-step) into its own register.
 __device__ __forceinline__ void launder(uint32_t& x) { asm volatile("" : "+v"(x)); }
 
+// V^T operand (d rows 32 db .. + 31, 16-key step st) of the row-major V
+// sub-tile at va.
+template <int D, int BLK, int BK>
+__device__ __forceinline__ bf16x8_t read_v(uint32_t va, int st, int db) {
+  using C = FwdCfg<D, BLK, BK>;
+  const uint32_t a = va + st * 4 * C::VPC + db * 256;
+  return __builtin_shufflevector(lds_read_tr8(a), lds_read_tr8(a + 2 * C::VPC), 0, 1, 2, 3, 4, 5,
+                                 6, 7);
+}
+
 // Unpipelined S^T = K Q^T of one sub-tile (QK) and/or O^T += V^T P^T of one
 // sub-tile (PV); the prologue and the drain of the pipeline.  ka[st] is this
-// lane's LDS address of its chunk for k-step st in K slot 0, va[st] the same
-// in V^T slot 0; kimm / vimm select the slot.
+// lane's LDS address of its chunk for k-step st in K slot 0, va its address
+// for key step 0, d block 0 in V slot 0; kimm / vimm select the slot.
 template <int D, int BLK, int BK, bool QK, bool PV>
 __device__ __forceinline__ void mfma_pair(const uint32_t* ka, uint32_t kimm, const bf16x8_t* qreg,
-                                          f32x16_t& snext, const uint32_t* va, uint32_t vimm,
+                                          f32x16_t& snext, uint32_t va, uint32_t vimm,
                                           const bf16x8_t* pprev, f32x16_t* o) {
   using C = FwdCfg<D, BLK, BK>;
   constexpr int NPV = 2 * C::DB;
@@ -147,7 +161,7 @@ __device__ __forceinline__ void mfma_pair(const uint32_t* ka, uint32_t kimm, con
     if constexpr (PV) {
       if (i < NPV) {
         const int st = i / C::DB, db = i % C::DB;
-        const bf16x8_t a = lds_read16(va[st] + vimm + db * C::VDB);
+        const bf16x8_t a = read_v<D, BLK, BK>(va + vimm, st, db);
         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pprev[st], o[db], 0, 0, 0);
       }
     }
@@ -192,7 +206,7 @@ __device__ __forceinline__ float softmax_sub(const f32x16_t& cur, float scale_lo
 template <int D, int BLK, int BK, int NPRE, int NL, typename Issue>
 __device__ __forceinline__ float pipeline_step(const uint32_t* ka, uint32_t kimm,
                                                const bf16x8_t* qreg, f32x16_t& snext,
-                                               const uint32_t* va, uint32_t vimm,
+                                               uint32_t va, uint32_t vimm,
                                                const bf16x8_t* pprev, f32x16_t* o, f32x16_t& cur,
                                                float scale_log2, float m_run, bf16x8_t* pcur,
                                                Issue&& issue) {
@@ -204,7 +218,7 @@ __device__ __forceinline__ float pipeline_step(const uint32_t* ka, uint32_t kimm
   auto read_op = [&](int i) -> bf16x8_t {
     if ((i & 1) == 0) return lds_read16(ka[i >> 1] + kimm);
     const int st = (i >> 1) / C::DB, db = (i >> 1) % C::DB;
-    return lds_read16(va[st] + vimm + db * C::VDB);
+    return read_v<D, BLK, BK>(va + vimm, st, db);
   };
   // load t is issued right after MFMA OFF + t * SP
   static_assert(NM % NL == 0, "loads spread evenly");
@@ -250,11 +264,16 @@ __device__ __forceinline__ float pipeline_step(const uint32_t* ka, uint32_t kimm
   // load if it has one, and either EPM (fma, exp) pairs or its share of the
   // 8 packs and 14 sums of the second half
   constexpr int TAIL = 22;
-  __builtin_amdgcn_sched_group_barrier(0x100, NPRE, 0);
+  __builtin_amdgcn_sched_group_barrier(0x100, NPRE + NPRE / 2, 0);
 #pragma unroll
   for (int i = 0; i < NM; ++i) {
     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    if (i + NPRE < NM) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    if (i + NPRE < NM) {  // a V operand takes two reads
+      if (((i + NPRE) & 1) != 0)
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      else
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
     if (has_load(i)) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read
     if (i < NM / 2) {
       __builtin_amdgcn_sched_group_barrier(0x002, EPM, 0);  // v_fma
@@ -309,7 +328,7 @@ template <int D, int BLK, int BK, bool DENSE, int KSP>
 __global__ void __launch_bounds__(BLK * 2 * KSP)
     __attribute__((amdgpu_waves_per_eu(KSP == 1 ? fwd_waves_per_simd<D, BLK>() : BLK / 64)))
     sparse_fwd_bf16_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K,
-                           const __bf16* __restrict__ Vt, const int32_t* __restrict__ row_ptr,
+                           const __bf16* __restrict__ V, const int32_t* __restrict__ row_ptr,
                            const int32_t* __restrict__ col_idx, int64_t col_len,
                            __bf16* __restrict__ O, float* __restrict__ lse,
                            float* __restrict__ bstat, const int* __restrict__ order, int n_q,
@@ -320,7 +339,7 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
   constexpr int BPI = C::BPI;
   constexpr int NT = C::NT * KSP;
   constexpr int NWV = C::NW * KSP;
-  // per key split: K ring at smem, V^T ring at smem + RING; slot x at + x*SUB
+  // per key split: K ring at smem, V ring at smem + RING; slot x at + x*SUB
   __shared__ __attribute__((aligned(1024))) char smem[KSP * 2 * C::RING];
   __shared__ uint16_t list[kMaxList];
 
@@ -343,7 +362,7 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
   const size_t head = (size_t)bh * n_pad * D;
   const uint32_t head_bytes = (uint32_t)((size_t)n_pad * D * 2);
   const i32x4_t krs = rsrc_words(K + head, head_bytes);
-  const i32x4_t vrs = rsrc_words(Vt + head, head_bytes);
+  const i32x4_t vrs = rsrc_words(V + head, head_bytes);
 
   // this lane's query row and its Q^T operand (8 bf16 per k-step).  Padding
   // rows take Q = 0, so their scores stay finite whatever the padding holds
@@ -408,21 +427,20 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
   const int S_real = KSP == 1 ? nb * NS : max(0, min(nb_trip, nb - nb0)) * NS;
   const int S = (NS == 1) ? (nb_trip + R - 1) / R * R : nb_trip * NS;
 
-  // per-lane LDS addresses of the operand reads in K slot 0 / V^T slot 0; the
-  // slot and the d sub-block are immediates
+  // per-lane LDS addresses of the operand reads in K slot 0 / V slot 0; the
+  // slot, and for V the key step and the d block, are immediates
   char* const ring = smem + sp * 2 * C::RING;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
-  uint32_t ka[C::KS], va[2];
+  uint32_t ka[C::KS];
 #pragma unroll
   for (int st = 0; st < C::KS; ++st)
     ka[st] = lds0 + l32 * C::KROW + (kswz<D, BLK, BK>(l32, 2 * st + g) << 4);
-#pragma unroll
-  for (int st = 0; st < 2; ++st)
-    va[st] = lds0 + C::RING + (l32 >> 2) * 256 +
-             (((l32 & 3) << 2) + ((2 * st + g) ^ ((l32 >> 2) & 3))) * 16;
+  uint32_t va = lds0 + C::RING + g * C::VPC + ((lane >> 2) & 3) * 64 + ((lane >> 4) & 1) * 32 +
+                (lane & 3) * 8;
   // per-lane global offsets of the direct loads (LDS position o of a K sub-tile
-  // holds row o / KROW, chunk kswz(row, (o % KROW) / 16); V^T is stored as the
-  // LDS image)
+  // holds row o / KROW, chunk kswz(row, (o % KROW) / 16); of a V sub-tile, key
+  // 4 (o / VPC) + (o % 256) / 64 at d block (o % VPC) / 256, and 1 KiB of LDS is
+  // 1 KiB of V, so further loads are at + u * 1024)
   uint32_t koffs[C::LPW];
 #pragma unroll
   for (int u = 0; u < C::LPW; ++u) {
@@ -430,9 +448,15 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
     const int row = o / C::KROW;
     koffs[u] = (uint32_t)(row * C::KROW + (kswz<D, BLK, BK>(row, (o % C::KROW) >> 4) << 4));
   }
-  const uint32_t voff0 = (uint32_t)(w * C::LPW * 1024 + lane * 16);
+  uint32_t voff0;
+  {
+    const int o = w * C::LPW * 1024 + lane * 16;
+    const int rem = o % C::VPC;
+    voff0 = (uint32_t)((4 * (o / C::VPC) + ((rem >> 6) & 3)) * C::KROW + (rem >> 8) * 64 +
+                       (rem & 63));
+  }
 
-  // key sub-tile (block j, part) -> K slot x / V^T slot x
+  // key sub-tile (block j, part) -> K slot x / V slot x
   auto load_k = [&](int x, int j, int part) {
 #pragma unroll
     for (int u = 0; u < C::LPW; ++u)
@@ -461,9 +485,9 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
 
   if (S > 0) {
     int jc[BPI], jn[BPI];  // blocks of this loop pass's sub-tiles and the next pass's
-    // prologue: K sub-tiles 0..R-1, V^T sub-tiles 0..R-3 (past the end of
+    // prologue: K sub-tiles 0..R-1, V sub-tiles 0..R-3 (past the end of
     // the stream the last block again, so that no slot holds stale bytes);
-    // zero V^T slot R-1 and the probabilities of "sub-tile -1"; scores of
+    // zero V slot R-1 and the probabilities of "sub-tile -1"; scores of
     // sub-tile 0
 #pragma unroll
     for (int x = 0; x < BPI; ++x) {
@@ -488,7 +512,7 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
     // Sub-iteration s = R*u + H (H static).  On entry the raw scores of s are
     // in sc[H & 1] and the probabilities of s-1 in pb[(H + 1) & 1].  The
     // matrix cores compute the scores of s+1 (K slot (H+1) % R) alternating
-    // with P V of s-1 (V^T slot (H-1) % R); the VALU exponentiates s.  A
+    // with P V of s-1 (V slot (H-1) % R); the VALU exponentiates s.  A
     // rescale found necessary for s is applied after P V(s-1), before P V(s).
     // The scores computed for sub-tile S (after the last) are never used; the
     // first P V multiplies zero probabilities with the zeroed slot.
@@ -499,9 +523,8 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
       f32x16_t& nxt = sc[(H + 1) & 1];
 #pragma unroll
       for (int st = 0; st < C::KS; ++st) launder(ka[st]);
-      launder(va[0]);
-      launder(va[1]);
-      // K sub-tile s+1 and V^T sub-tile s-1 (both issued in sub-iteration
+      launder(va);
+      // K sub-tile s+1 and V sub-tile s-1 (both issued in sub-iteration
       // s-3, so not among the last two sub-iterations' loads that the count
       // leaves in flight) have landed for every wave, and every wave is done
       // with sub-iteration s-1.  Every sub-iteration issues the same loads
@@ -511,7 +534,7 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
       constexpr int HV = H + R - 2;  // pass-relative index of sub-tile s+R-2
       const int jk = jn[H / NS];
       const int jv = (HV < R) ? jc[(HV < R ? HV : 0) / NS] : jn[(HV < R ? 0 : HV - R) / NS];
-      // refill: K slot H <- K sub-tile s+R, V^T slot (H+R-2) % R <- sub-tile s+R-2
+      // refill: K slot H <- K sub-tile s+R, V slot (H+R-2) % R <- sub-tile s+R-2
       auto issue = [&](int t) {
         if (t < C::LPW) {
           dma16(lds0 + H * C::SUB + (w * C::LPW + t) * 1024, krs, koffs[t],
@@ -594,7 +617,7 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
       }
     }
     // drain: P V of the last sub-tile S-1 (odd, so its probabilities are
-    // pb[1]).  Its V^T slot was filled in sub-iteration S-3, one part by each
+    // pb[1]).  Its V slot was filled in sub-iteration S-3, one part by each
     // wave, and the last barrier only covered loads up to S-4: every wave
     // waits for all of its own loads (the later ones included, which nothing
     // reads, so that none lands after the workgroup's LDS is handed on), then
@@ -700,50 +723,29 @@ __global__ void __launch_bounds__(kOrderChunk)
   }
 }
 
-// V [BH][n_pad][D] -> V^T in the LDS image of its 32-key sub-tiles: sub-tile y
-// of a head is SUB contiguous bytes, 16-byte chunk p of it holds d = 4*(p/16) +
-// (p/4)%4 and key positions 8c..8c+7 with c = (p%4) ^ ((p/16)%4); position q
-// of a 32-key sub-tile holds key (q & ~15) | perm16(q & 15).  One workgroup
-// transposes 64 keys (two sub-tiles) x D of one head through LDS.
-template <int D>
-__global__ void __launch_bounds__(256)
-    transpose_v_kernel(const __bf16* __restrict__ V, __bf16* __restrict__ Vt, int n_pad) {
-  constexpr int TK = 64;
-  constexpr int LD = D + 2;  // padded LDS row (elements)
-  __shared__ __bf16 tile[TK * LD];
-  const int bh = blockIdx.y;
-  const int n0 = blockIdx.x * TK;
-  const __bf16* src = V + (size_t)bh * n_pad * D + (size_t)n0 * D;
-  __bf16* dst = Vt + (size_t)bh * n_pad * D + (size_t)n0 * D;
-  for (int c = threadIdx.x; c < TK * D / 8; c += 256) {
-    const int row = c / (D / 8);
-    const int col = (c % (D / 8)) * 8;
-    const bf16x8_t v = *reinterpret_cast<const bf16x8_t*>(src + (size_t)row * D + col);
-#pragma unroll
-    for (int t = 0; t < 8; ++t) tile[row * LD + col + t] = v[t];
-  }
-  __syncthreads();
-  // output chunk q: sub-tile q / (4D), chunk p = q % (4D) of it
-  for (int q = threadIdx.x; q < TK * D / 8; q += 256) {
-    const int y = q / (4 * D);
-    const int p = q % (4 * D);
-    const int line = p >> 4;
-    const int d = line * 4 + ((p >> 2) & 3);
-    const int c = (p & 3) ^ (line & 3);
-    bf16x8_t v;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int pos = c * 8 + t;
-      const int key = y * 32 + ((pos & ~15) | perm16(pos & 15));
-      v[t] = tile[key * LD + d];
-    }
-    *reinterpret_cast<bf16x8_t*>(dst + (size_t)q * 8) = v;
-  }
+// Workspace layout: room for a copy of V (B*H*n_pad*D bf16), then the dispatch
+// order (one int per row) at the next 256-byte boundary.
+size_t order_offset(int BH, int n_pad, int d) {
+  return ((size_t)BH * n_pad * d * 2 + 255) / 256 * 256;
 }
 
-// Workspace layout: V^T (B*H*n_pad*D bf16), then the dispatch order (one int
-// per row) at the next 256-byte boundary.
-size_t vt_bytes(int BH, int n_pad, int d) { return ((size_t)BH * n_pad * d * 2 + 255) / 256 * 256; }
+__global__ void __launch_bounds__(256)
+    copy_v_kernel(const f32x4_t* __restrict__ src, f32x4_t* __restrict__ dst, size_t n) {
+  for (size_t x = (size_t)blockIdx.x * 256 + threadIdx.x; x < n; x += (size_t)gridDim.x * 256)
+    dst[x] = src[x];
+}
+
+// V for the kernel: the caller's, or, where o is written over it, a copy of it
+// in `room` (rows still to come read the values that finished rows overwrite).
+const void* readable_v(const void* v, const void* o, size_t bytes, void* room,
+                       hipStream_t stream) {
+  const char* vb = static_cast<const char*>(v);
+  const char* ob = static_cast<const char*>(o);
+  if (ob + bytes <= vb || vb + bytes <= ob) return v;
+  hipLaunchKernelGGL(copy_v_kernel, dim3(2048), dim3(256), 0, stream,
+                     static_cast<const f32x4_t*>(v), static_cast<f32x4_t*>(room), bytes / 16);
+  return room;
+}
 
 // Two key splits per row where a call's rows leave CUs with one workgroup or
 // none: a wave alone on its SIMD waits out its own exponentials and barriers.
@@ -765,8 +767,8 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, int B, int H,
   const int n_q = n_pad / BLK;
   const int n_k = n_pad / BK;
   const int rows = BH * n_q;
-  __bf16* vt = static_cast<__bf16*>(workspace);
-  int* order = reinterpret_cast<int*>(static_cast<char*>(workspace) + vt_bytes(BH, n_pad, D));
+  v = readable_v(v, o, (size_t)BH * n_pad * D * 2, workspace, stream);
+  int* order = reinterpret_cast<int*>(static_cast<char*>(workspace) + order_offset(BH, n_pad, D));
   if (KSP > 1) {
     order = nullptr;  // every row starts at once
   } else {
@@ -774,12 +776,9 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, int B, int H,
     hipLaunchKernelGGL(order_rows_kernel, dim3((per_xcd + kOrderChunk - 1) / kOrderChunk, 8),
                        dim3(kOrderChunk), 0, stream, row_ptr, col_len, rows, n_k, order);
   }
-  dim3 tgrid(n_pad / 64, BH);
-  hipLaunchKernelGGL(transpose_v_kernel<D>, tgrid, dim3(256), 0, stream,
-                     static_cast<const __bf16*>(v), vt, n_pad);
   hipLaunchKernelGGL((sparse_fwd_bf16_kernel<D, BLK, BK, false, KSP>), dim3(rows),
                      dim3(FwdCfg<D, BLK, BK>::NT * KSP), 0, stream, static_cast<const __bf16*>(q),
-                     static_cast<const __bf16*>(k), static_cast<const __bf16*>(vt), row_ptr,
+                     static_cast<const __bf16*>(k), static_cast<const __bf16*>(v), row_ptr,
                      col_idx, col_len, static_cast<__bf16*>(o), lse, nullptr, order, n_q, n_k, N,
                      n_pad, scale * kLog2e);
   return hipGetLastError();
@@ -793,16 +792,13 @@ hipError_t launch_dense(const void* q, const void* k, const void* v, int B, int 
                         int n_pad, float scale, void* o, float* lse, float* stat, void* workspace,
                         hipStream_t stream) {
   const int BH = B * H;
+  v = readable_v(v, o, (size_t)BH * n_pad * D * 2, workspace, stream);
   const int n_q = n_pad / BLK;
   const int n_k = n_pad / BK;
   const int rows = BH * n_q;
-  __bf16* vt = static_cast<__bf16*>(workspace);
-  dim3 tgrid(n_pad / 64, BH);
-  hipLaunchKernelGGL(transpose_v_kernel<D>, tgrid, dim3(256), 0, stream,
-                     static_cast<const __bf16*>(v), vt, n_pad);
   hipLaunchKernelGGL((sparse_fwd_bf16_kernel<D, BLK, BK, true, KSP>), dim3(rows),
                      dim3(FwdCfg<D, BLK, BK>::NT * KSP), 0, stream, static_cast<const __bf16*>(q),
-                     static_cast<const __bf16*>(k), static_cast<const __bf16*>(vt), nullptr,
+                     static_cast<const __bf16*>(k), static_cast<const __bf16*>(v), nullptr,
                      nullptr, 0, static_cast<__bf16*>(o), lse, stat, nullptr, n_q, n_k, N, n_pad,
                      scale * kLog2e);
   return hipGetLastError();
@@ -860,8 +856,7 @@ hipError_t launch_dense_bf16(int d, int blk, int blk_k, const void* q, const voi
 }
 
 size_t sparse_fwd_bf16_workspace(int B, int H, int n_pad, int d, int n_q) {
-  // V^T in sub-tile LDS images, then the rows' dispatch order
-  return vt_bytes(B * H, n_pad, d) + (size_t)B * H * n_q * sizeof(int);
+  return order_offset(B * H, n_pad, d) + (size_t)B * H * n_q * sizeof(int);
 }
 
 }  // namespace losa

@@ -81,3 +81,22 @@ def test_key_split(L, case):
     assert torch.equal(dense, dense1) and torch.equal(mass, mass1)
     m_ref, _ = O.block_masses(f64(q[:, :2]), f64(k[:, :2]), N, Cq, Ck, scale)
     assert np.abs(f64(mass[:, :2]) - m_ref).max() <= 1e-4
+
+
+@pytest.mark.parametrize("H,N", [(2, 600), (40, 1000)])   # split and not
+def test_output_over_v(L, H, N):
+    """o written over v gives what separate buffers give, in both calls."""
+    n_pad = O.padded_len(N, 128, 128)
+    n = n_pad // 128
+    g = torch.Generator().manual_seed(77)
+    q, k, v = (torch.randn((1, H, n_pad, 128), generator=g).bfloat16().cuda() for _ in range(3))
+    rp = (torch.arange(H * n + 1) * n).int().cuda()
+    ci = torch.arange(n, dtype=torch.int32).repeat(H * n).cuda()
+    want = L.losa_sparse_attn_fwd(q, k, v, N, 128, 128, rp, ci)
+    for call in (lambda x: L.losa_sparse_attn_fwd(q, k, x, N, 128, 128, rp, ci, out=x),
+                 lambda x: L.losa_sparse_attn_fwd_noalloc(q, k, x, N, 128, 128, rp, ci, out=x),
+                 lambda x: L.losa_construct(q, k, x, N, 128, 128, out=x)[0]):
+        x = v.clone()
+        got = call(x)
+        torch.cuda.synchronize()
+        assert got.data_ptr() == x.data_ptr() and torch.equal(got, want)
