@@ -22,10 +22,11 @@
 // order through LDS at the end; two waves per SIMD cover each other's softmax.
 //
 // Bound: the fp32 matrix rate (157 TFLOP/s).  Attention over full rows, d =
-// 128: 126 TFLOP/s at N = 8,192 x 4 heads, 121 at 4,096, 96 at 4,480 (the last
-// of five rounds 38 % full), 33 at 512 x 4 (a launch with 128 tiles of one
-// round).  A thread per query row with plain fma and its keys in LDS, which
-// this replaced, ran 7.7 TFLOP/s at N = 4,437 x 4 (5.2 ms, now 0.43).
+// 128: 126 TFLOP/s at N = 8,192 x 4 heads, 121 at 4,096, 104 at 4,480 (the last
+// round a fifth full), 33 at 512 x 4 (128 tiles of one round).  A thread per query row with plain fma and its keys in LDS, which
+// this replaced, ran 7.7 TFLOP/s at N = 4,437 x 4 (5.2 ms, now 0.41).
+// The construction step's masses take one sweep over the keys (175 us at N =
+// 4,437 x 4 heads and 11 us for their reduction; two sweeps: 238 + 175).
 //
 // Masking and padding follow the bf16 kernels: keys >= N never enter a
 // softmax, query rows >= N read Q as 0 and get O = 0 and lse = -inf, and so do
@@ -257,8 +258,8 @@ __global__ void __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_pe
     attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
                     const float* __restrict__ V, const int32_t* __restrict__ row_ptr,
                     const int32_t* __restrict__ col_idx, int64_t col_len, float* __restrict__ O,
-                    float* __restrict__ lse, int blk, int bk_sub, int n_k, int N, int n_pad,
-                    float scale_log2, int dense) {
+                    float* __restrict__ lse, int tile0, int blk, int bk_sub, int n_k, int N,
+                    int n_pad, float scale_log2, int dense) {
   using T = F32Tile<D, M>;
   using A = F32Acc<M>;
   constexpr int NWV = kF32Waves;
@@ -275,7 +276,7 @@ __global__ void __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_pe
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lm = lane % M, g = lane / M;
   const int tiles = n_pad / M;  // per head
-  const int x0 = xcd_remap(blockIdx.x, gridDim.x);
+  const int x0 = tile0 + xcd_remap(blockIdx.x, gridDim.x);
   const int bh = x0 / tiles;
   const int row0 = (x0 - bh * tiles) * M;
   const int r = bh * (n_pad / blk) + row0 / blk;
@@ -534,6 +535,113 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// Block statistics of one query block over a range of key blocks:
+// stat[bh][j][q] = log2 of query q's unnormalised probability sum over block
+// j.  Waves and key blocks as in mass_f32_kernel.
+template <int D, int BLK>
+__global__ void __launch_bounds__(256)
+    stat_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+                    float* __restrict__ stat, int bk_sub, int per_wg, int n_k, int n_kb, int N,
+                    int n_pad, float scale_log2) {
+  constexpr int M = 32;
+  constexpr int RW = BLK / M;
+  constexpr int KSP = 4 / RW;
+  using T = F32Tile<D, M>;
+  using A = F32Acc<M>;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rw = w % RW, sp = w / RW;
+  const int lm = lane % M, g = lane / M;
+  const int n_q = n_pad / BLK;
+  const int bh = blockIdx.x / n_q;
+  const int i = blockIdx.x - bh * n_q;
+  const int bk = bk_sub * CK;
+  const int j0 = blockIdx.y * per_wg + sp, j1 = min(n_kb, (int)(blockIdx.y + 1) * per_wg);
+  if (j0 >= j1) return;
+  const int qrow = i * BLK + rw * M + lm;
+  const float* Kh = K + (size_t)bh * n_pad * D;
+  f32x4_t qr[T::QI];
+  load_q<D, M>(qr, Q + (size_t)bh * n_pad * D, qrow, g, qrow < N, scale_log2);
+  f32x4_t ring[kLead];
+#pragma unroll
+  for (int c = 0; c < kLead; ++c) ring[c] = load_k<D, M>(Kh, j0 * bk, c, lm, g);
+  for (int j = j0; j < j1; j += KSP) {
+    // m: reference of the block's sum, the same in both lanes of a query
+    float m = kNegBig, l = 0.f;
+    const int subs = min(bk_sub, (N - j * bk + CK - 1) / CK);  // those that hold a valid key
+    for (int u = 0; u < subs; ++u) {
+      const int key0 = j * bk + u * CK;
+      const int next = u + 1 < subs ? key0 + CK : (j + KSP < j1 ? (j + KSP) * bk : key0);
+      typename A::type s[T::KT];
+      scores<D, M>(ring, qr, g, N - key0, s, [&](int c) {
+        const int n = c + kLead;
+        ring[c % kLead] = load_k<D, M>(Kh, n < T::KC ? key0 : next, n % T::KC, lm, g);
+      });
+      const float m_new = fmaxf(m, tile_max<D, M>(s));
+      l = l * fast_exp2(m - m_new) + tile_exp<D, M>(s, m_new);
+      m = m_new;
+    }
+    const float sum = l + __shfl_xor(l, 32);
+    if (g == 0) stat[((size_t)bh * n_k + j) * n_pad + qrow] = __log2f(sum) + m;
+  }
+}
+
+// Masses of one query block from its block statistics: each query's normaliser
+// over the n_kb key blocks (fp64 sums), then per key block the mean over the
+// valid queries.  Blocks past n_kb hold no valid key.
+template <int BLK>
+__global__ void __launch_bounds__(256)
+    mass_of_stat_f32_kernel(const float* __restrict__ stat, float* __restrict__ mass, int n_k,
+                            int n_kb, int N, int n_pad) {
+  constexpr int PT = 256 / BLK;  // threads per query
+  __shared__ float mx[256];
+  __shared__ double sm[256];
+  __shared__ float lse2[BLK];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int n_q = n_pad / BLK;
+  const int bh = blockIdx.x / n_q;
+  const int i = blockIdx.x - bh * n_q;
+  const float* base = stat + (size_t)bh * n_k * n_pad + i * BLK;
+  float* mrow = mass + (size_t)blockIdx.x * n_k;
+  const int rows_valid = min(BLK, N - i * BLK);
+  if (rows_valid <= 0) {
+    for (int j = t; j < n_k; j += 256) mrow[j] = 0.f;
+    return;
+  }
+  const int q = t % BLK, part = t / BLK;
+  float m = kNegBig;
+  for (int j = part; j < n_kb; j += PT) m = fmaxf(m, base[(size_t)j * n_pad + q]);
+  double l = 0.0;
+  for (int j = part; j < n_kb; j += PT) l += (double)fast_exp2(base[(size_t)j * n_pad + q] - m);
+  mx[t] = m;
+  sm[t] = l;
+  __syncthreads();
+  if (t < BLK) {
+    float mm = m;
+#pragma unroll
+    for (int y = 1; y < PT; ++y) mm = fmaxf(mm, mx[y * BLK + t]);
+    double lt = 0.0;
+#pragma unroll
+    for (int y = 0; y < PT; ++y) lt += sm[y * BLK + t] * (double)fast_exp2(mx[y * BLK + t] - mm);
+    lse2[t] = mm + __log2f((float)lt);
+  }
+  __syncthreads();
+  const float inv_rows = 1.0f / (float)rows_valid;
+  for (int j = w; j < n_k; j += 4) {
+    float acc = 0.f;
+    if (j < n_kb) {
+#pragma unroll
+      for (int e = 0; e < BLK / 64; ++e) {
+        const int row = lane + 64 * e;
+        if (row < rows_valid) acc += fast_exp2(base[(size_t)j * n_pad + row] - lse2[row]);
+      }
+    }
+    acc = wave_sum(acc);
+    if (lane == 0) mrow[j] = acc * inv_rows;
+  }
+}
+
 // log2 normalisers -> natural logs, -inf on padding rows.
 __global__ void __launch_bounds__(256)
     lse_natural_kernel(float* __restrict__ lse, int N, int n_pad, int64_t total) {
@@ -541,29 +649,36 @@ __global__ void __launch_bounds__(256)
   if (x < total) lse[x] = x % n_pad < N ? lse[x] * kLn2 : -INFINITY;
 }
 
-// Tile height of a call with `tiles` 32-row tiles.  A workgroup fills a CU and
-// a row's keys are not split over workgroups, so the time goes in rounds of
-// 256 tiles; a round of 16-row tiles has half the work but the same K/V
-// traffic.  Measured, one round of 32-row against one of 16-row tiles: 79 /
-// 44 us at d = 128 and 48 / 25 us at d = 64 (N = 2,048, 4 heads), scores only 79 / 64
-// us (N = 4,437, d = 128).  So at 560 tiles attention takes 16 rows (428
-// against 455 us) and at 512 it takes 32 (284 against 319 us).
+// Tile heights of a call with `tiles` 32-row tiles: how many of them run as
+// such, the rest as twice as many 16-row tiles.  A workgroup fills a CU and a
+// row's keys are not split over workgroups, so the time goes in rounds of 256
+// tiles; a round of 16-row tiles has half the work but the same K/V traffic.
+// Measured, one round of 32-row against one of 16-row tiles: 79 / 44 us at d =
+// 128 and 48 / 25 us at d = 64 (N = 2,048, 4 heads).  So at d = 128 whole
+// rounds are 32 rows high, and what is left over, if it is 128 tiles or fewer,
+// one round of 16 rows (560 tiles: 397 us, all 32 rows 455, all 16 rows 428).
+// At d = 64 such a call takes 16 rows throughout (560 tiles: 218 us, mixed 228,
+// all 32 rows 260).  Scores only (79 / 64 us, N = 4,437, d = 128) take one
+// height for all.
 template <bool PV>
-bool wide_tiles(int64_t tiles) {
+int64_t wide_tiles(int d, int64_t tiles) {
+  const int64_t rest = tiles % 256;
+  if (PV) return rest > 128 || rest == 0 ? tiles : (d == 64 ? 0 : tiles - rest);
   const int64_t r32 = (tiles + 255) / 256, r16 = (2 * tiles + 255) / 256;
-  return PV ? 19 * r32 <= 10 * r16 : 5 * r32 <= 4 * r16;
+  return 5 * r32 <= 4 * r16 ? tiles : 0;
 }
 
 template <int D, int M, bool PV>
-hipError_t launch_attn(const void* q, const void* k, const void* v, int BH, int blk, int blk_k,
-                       int N, int n_pad, float scale, const int32_t* row_ptr,
+hipError_t launch_attn(const void* q, const void* k, const void* v, int tile0, int64_t tiles,
+                       int blk, int blk_k, int N, int n_pad, float scale, const int32_t* row_ptr,
                        const int32_t* col_idx, int64_t col_len, void* o, float* lse,
                        hipStream_t stream) {
-  hipLaunchKernelGGL((attn_f32_kernel<D, M, PV>), dim3(BH * (n_pad / M)),
-                     dim3(64 * kF32Waves), 0, stream, static_cast<const float*>(q),
-                     static_cast<const float*>(k), static_cast<const float*>(v), row_ptr, col_idx,
-                     col_len, static_cast<float*>(o), lse, blk, blk_k / CK, n_pad / blk_k, N,
-                     n_pad, scale * kLog2e, row_ptr == nullptr);
+  if (tiles == 0) return hipSuccess;
+  hipLaunchKernelGGL((attn_f32_kernel<D, M, PV>), dim3((uint32_t)tiles), dim3(64 * kF32Waves), 0,
+                     stream, static_cast<const float*>(q), static_cast<const float*>(k),
+                     static_cast<const float*>(v), row_ptr, col_idx, col_len,
+                     static_cast<float*>(o), lse, tile0, blk, blk_k / CK, n_pad / blk_k, N, n_pad,
+                     scale * kLog2e, row_ptr == nullptr);
   return hipGetLastError();
 }
 
@@ -572,17 +687,30 @@ hipError_t launch_attn_any(int d, int blk, int blk_k, const void* q, const void*
                            int BH, int N, int n_pad, float scale, const int32_t* row_ptr,
                            const int32_t* col_idx, int64_t col_len, void* o, float* lse,
                            hipStream_t stream) {
-  const bool wide = wide_tiles<PV>((int64_t)BH * (n_pad / 32));
-#define LOSA_F32_ATTN(DD, MM)                                                                     \
-  if (d == DD && wide == (MM == 32))                                                              \
-    return launch_attn<DD, MM, PV>(q, k, v, BH, blk, blk_k, N, n_pad, scale, row_ptr, col_idx,    \
-                                   col_len, o, lse, stream);
-  LOSA_F32_ATTN(64, 32)
-  LOSA_F32_ATTN(64, 16)
-  LOSA_F32_ATTN(128, 32)
-  LOSA_F32_ATTN(128, 16)
+  const int64_t tiles = (int64_t)BH * (n_pad / 32), wide = wide_tiles<PV>(d, tiles);
+  const int rest0 = (int)(2 * wide);  // first 16-row tile
+  hipError_t err = hipErrorInvalidValue;
+#define LOSA_F32_ATTN(DD)                                                                        \
+  if (d == DD) {                                                                                 \
+    err = launch_attn<DD, 32, PV>(q, k, v, 0, wide, blk, blk_k, N, n_pad, scale, row_ptr,        \
+                                  col_idx, col_len, o, lse, stream);                             \
+    if (err == hipSuccess)                                                                       \
+      err = launch_attn<DD, 16, PV>(q, k, v, rest0, 2 * (tiles - wide), blk, blk_k, N, n_pad,    \
+                                    scale, row_ptr, col_idx, col_len, o, lse, stream);           \
+  }
+  LOSA_F32_ATTN(64)
+  LOSA_F32_ATTN(128)
 #undef LOSA_F32_ATTN
-  return hipErrorInvalidValue;
+  return err;
+}
+
+// Key blocks per workgroup of the kernels that split a query block's keys over
+// workgroups: enough workgroups for four per CU, each with 256 keys at least.
+int key_blocks_per_wg(int rows, int n_k, int blk_k) {
+  const int want = rows < 1024 ? (1024 + rows - 1) / rows : 1;
+  const int least = 256 / blk_k > 1 ? 256 / blk_k : 1;
+  const int per_wg = (n_k + want - 1) / want;
+  return per_wg < least ? least : per_wg;
 }
 
 template <int D, int BLK>
@@ -597,14 +725,29 @@ hipError_t launch_mass(const void* q, const void* k, const float* lse2, float* m
                        kf, nullptr, mass, blk_k / CK, n_k, n_k, N, n_pad, scale * kLog2e);
     return hipGetLastError();
   }
-  // enough workgroups for four per CU, each with a few key blocks at least
-  const int want = rows < 1024 ? (1024 + rows - 1) / rows : 1;
-  const int least = 256 / blk_k > 1 ? 256 / blk_k : 1;
-  int per_wg = (n_k + want - 1) / want;
-  if (per_wg < least) per_wg = least;
+  const int per_wg = key_blocks_per_wg(rows, n_k, blk_k);
   hipLaunchKernelGGL((mass_f32_kernel<D, BLK, false>), dim3(rows, (n_k + per_wg - 1) / per_wg),
                      dim3(256), 0, stream, qf, kf, lse2, mass, blk_k / CK, per_wg, n_k, N, n_pad,
                      scale * kLog2e);
+  return hipGetLastError();
+}
+
+// Masses in one sweep over the keys: block statistics into `stat` ([BH][n_k]
+// [n_pad] floats), then their reduction.
+template <int D, int BLK>
+hipError_t launch_stat(const void* q, const void* k, float* stat, float* mass, int BH, int blk_k,
+                       int N, int n_pad, float scale, hipStream_t stream) {
+  const int rows = BH * (n_pad / BLK);
+  const int n_k = n_pad / blk_k, n_kb = (N + blk_k - 1) / blk_k;
+  const int per_wg = key_blocks_per_wg(rows, n_kb, blk_k);
+  hipLaunchKernelGGL((stat_f32_kernel<D, BLK>), dim3(rows, (n_kb + per_wg - 1) / per_wg),
+                     dim3(256), 0, stream, static_cast<const float*>(q),
+                     static_cast<const float*>(k), stat, blk_k / CK, per_wg, n_k, n_kb, N, n_pad,
+                     scale * kLog2e);
+  hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL(mass_of_stat_f32_kernel<BLK>, dim3(rows), dim3(256), 0, stream, stat, mass,
+                     n_k, n_kb, N, n_pad);
   return hipGetLastError();
 }
 
@@ -654,9 +797,28 @@ hipError_t launch_calibrate_f32(int d, int blk, int blk_k, const void* q, const 
 hipError_t launch_construct_f32(int d, int blk, int blk_k, const void* q, const void* k,
                                 const void* v, int B, int H, int N, int n_pad, float scale,
                                 void* o, float* mass, float* lse, hipStream_t stream) {
-  // O is written last: until then its first floats hold the log2 normalisers
-  const hipError_t err = masses(d, blk, blk_k, q, k, B * H, N, n_pad, scale, mass,
-                                static_cast<float*>(o), stream);
+  // O is written last: until then it holds the block statistics, one float per
+  // query and key block, where its d floats per query are enough for them, and
+  // the log2 normalisers otherwise (the masses then take a sweep of their own)
+  // (over an input it can hold neither: the mass kernel then finds its own
+  // normalisers)
+  const size_t bytes = (size_t)B * H * n_pad * d * sizeof(float);
+  float* const scratch =
+      overlap(o, q, bytes) || overlap(o, k, bytes) || overlap(o, v, bytes) ? nullptr
+                                                                           : static_cast<float*>(o);
+  hipError_t err = hipErrorInvalidValue;
+  if (scratch != nullptr && n_pad / blk_k <= d) {
+#define LOSA_F32_STAT(DD, BB) \
+  if (d == DD && blk == BB)   \
+    err = launch_stat<DD, BB>(q, k, scratch, mass, B * H, blk_k, N, n_pad, scale, stream);
+    LOSA_F32_STAT(64, 64)
+    LOSA_F32_STAT(64, 128)
+    LOSA_F32_STAT(128, 64)
+    LOSA_F32_STAT(128, 128)
+#undef LOSA_F32_STAT
+  } else {
+    err = masses(d, blk, blk_k, q, k, B * H, N, n_pad, scale, mass, scratch, stream);
+  }
   if (err != hipSuccess) return err;
   return launch_sparse_fwd_f32(d, blk, blk_k, q, k, v, B, H, N, n_pad, scale, nullptr, nullptr, 0,
                                o, lse, stream);

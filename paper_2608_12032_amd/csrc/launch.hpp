@@ -15,6 +15,12 @@ __host__ __device__ inline int padded_len(int N, int block_q, int block_k) {
   return (N + L - 1) / L * L;
 }
 
+// Whether two buffers of `bytes` bytes share any.
+inline bool overlap(const void* a, const void* b, size_t bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + bytes && y < x + bytes;
+}
+
 // blk = query block rows, blk_k = key block keys (blk, or 32)
 // stat == nullptr: two sweeps over the keys, lse optional.
 // stat != nullptr: one sweep that writes the block statistics

@@ -739,9 +739,7 @@ __global__ void __launch_bounds__(256)
 // in `room` (rows still to come read the values that finished rows overwrite).
 const void* readable_v(const void* v, const void* o, size_t bytes, void* room,
                        hipStream_t stream) {
-  const char* vb = static_cast<const char*>(v);
-  const char* ob = static_cast<const char*>(o);
-  if (ob + bytes <= vb || vb + bytes <= ob) return v;
+  if (!overlap(v, o, bytes)) return v;
   hipLaunchKernelGGL(copy_v_kernel, dim3(2048), dim3(256), 0, stream,
                      static_cast<const f32x4_t*>(v), static_cast<f32x4_t*>(room), bytes / 16);
   return room;

@@ -1,10 +1,12 @@
 """fp32 kernels at the edges of their tiles.
 
-The attention kernel works on 32-row tiles or, where that fills the chip
-better (a call of at most 128 of the former, for one), on 16-row tiles; its eight waves share a row's 32-key sub-tiles.  The
-mass kernel splits a row's key blocks over workgroups when the normalisers have
-room (the caller's lse, or the construction step's output) and sweeps the keys
-itself when they have none.  Each combination of tile height, head size, block
+The attention kernel works on 32-row tiles, 256 at a time, and on 16-row tiles
+for a rest of 128 of the former or fewer (at d = 64 then throughout); its eight
+waves share a row's 32-key sub-tiles.  The masses come from block statistics in
+the construction step's output where there are no more key blocks than floats
+in a row of it, and else from a kernel that splits a row's key blocks over
+workgroups when the normalisers have room (the caller's lse, or that output)
+and sweeps the keys itself when they have none.  Each combination of tile height, head size, block
 shape and ragged length, with fewer, as many and more sub-tiles than waves,
 against the oracle on every row.  Bars: the fp32 path's (1e-4 on outputs and
 masses, 1e-3 on lse)."""
@@ -16,10 +18,12 @@ from oracle import losa_oracle as O
 
 pytestmark = pytest.mark.gpu
 
-# (heads, d, block_q, block_k, N): 16-row tiles, then 32-row ones
+# (heads, d, block_q, block_k, N): 16-row tiles, then 32-row ones, both, and more
+# key blocks than the statistics have room for
 CASES = [(2, 64, 64, 64, 33), (2, 128, 128, 128, 257), (3, 128, 64, 32, 289), (2, 64, 128, 32, 480),
          (12, 64, 64, 64, 385), (10, 128, 128, 128, 511), (9, 128, 128, 32, 487),
-         (17, 64, 128, 128, 256), (14, 128, 64, 64, 321)]
+         (17, 64, 128, 128, 256), (14, 128, 64, 64, 321), (9, 64, 64, 64, 950),
+         (22, 128, 128, 32, 380), (1, 64, 64, 32, 2100), (1, 64, 64, 32, 2040)]
 
 
 @pytest.fixture(scope="module")
@@ -60,6 +64,10 @@ def test_f32_tiles(L, case):
     d_ref, _ = O.dense_attention(qh, kh, vh, N, scale)
     assert np.abs(f64(o)[:, :, :N] - d_ref[:, :, :N]).max() <= 1e-4
     assert np.all(f64(o)[:, :, N:] == 0)
+    x = q.clone()                              # the output over an input
+    o2, mass4 = L.losa_construct(x, k, v, N, Cq, Ck, out=x)
+    torch.cuda.synchronize()
+    assert torch.equal(o2, o) and np.abs(f64(mass4) - m_ref).max() <= 1e-4
 
     # a support with empty, single-block and full rows, repeated and stray ids
     rng = np.random.default_rng(800 + CASES.index(case))
