@@ -8,9 +8,9 @@
 // independent waves: while one waits at its workgroup barrier or on its
 // exponentials, another keeps the matrix core busy.  The workgroup first
 // turns its CSR entries into a sorted list of distinct valid block ids in LDS
-// (per-block flags, then a ballot compaction), which realises Eq. (4)'s set
-// semantics exactly: a repeated id counts once, ids outside [0, n_k) are
-// dropped.
+// (as they are where they are that already, else by per-block flags and a
+// ballot compaction), which realises Eq. (4)'s set semantics exactly: a repeated
+// id counts once, ids outside [0, n_k) are dropped.
 //
 // Orientation.  Per 32-key sub-tile the wave computes S^T = K Q^T with
 // v_mfma_f32_32x32x16_bf16 (A = K rows from LDS, B = the wave's Q^T held in
@@ -116,7 +116,7 @@ struct FwdCfg {
   static_assert(SUB % (1024 * NW) == 0, "sub-tile must split into whole wave loads");
   static_assert(R % NS == 0 && R >= 4 && (R & 1) == 0, "ring holds whole key blocks");
   static_assert(KS == 2 * DB, "QK and PV steps alternate one to one");
-  static_assert(2 * RING >= kMaxList + 4 * NW, "list-building scratch fits the rings");
+  static_assert(2 * RING >= kMaxList, "list-building scratch fits the rings");
 };
 
 // Swizzled chunk of K chunk c in sub-tile row `row`.
@@ -342,6 +342,7 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
   // per key split: K ring at smem, V ring at smem + RING; slot x at + x*SUB
   __shared__ __attribute__((aligned(1024))) char smem[KSP * 2 * C::RING];
   __shared__ uint16_t list[kMaxList];
+  __shared__ int wcount[NWV];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -377,43 +378,65 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
   }
 
   // ---- the row's distinct valid key blocks, ascending ---------------------
-  // (flags and per-wave counts live in the rings, unused until the first load)
+  // (the flags live in the rings, unused until the first load)
   int nb = 0;
   if constexpr (DENSE) {
     nb = (N + BK - 1) / BK;
     for (int j = tid; j < nb; j += NT) list[j] = (uint16_t)j;
     __syncthreads();
   } else {
-    uint8_t* const flag = reinterpret_cast<uint8_t*>(smem);
-    int* const wcount = reinterpret_cast<int*>(smem + kMaxList);
-    for (int j = tid; j < n_k; j += NT) flag[j] = 0;
-    __syncthreads();
     int64_t e0 = row_ptr[r], e1 = row_ptr[r + 1];
     e0 = e0 < 0 ? 0 : (e0 > col_len ? col_len : e0);
     e1 = e1 < e0 ? e0 : (e1 > col_len ? col_len : e1);
-    for (int64_t e = e0 + tid; e < e1; e += NT) {
-      const int j = col_idx[e];
-      if (j >= 0 && j < n_k) flag[j] = 1;
+    // a row as the selection writes it, valid ids strictly ascending, is its
+    // own list: one barrier, where building it from flags takes two and two
+    // more per NT key blocks (with the epilogue's stores and the later wait
+    // for unread loads: 255 -> 247 us at 3,072 rows of 7 blocks, 28.3 -> 26.5
+    // at 156 rows of 12)
+    const int len = (int)(e1 - e0 < n_k ? e1 - e0 : n_k);
+    bool sorted = e1 - e0 <= n_k;
+    for (int x = tid; x < len; x += NT) {
+      const int j = col_idx[e0 + x];
+      const int before = x > 0 ? col_idx[e0 + x - 1] : -1;
+      sorted = sorted && j > before && j < n_k;
+      list[x] = (uint16_t)j;
     }
+    if (lane == 0) wcount[wv] = 1;
+    if (!sorted) wcount[wv] = 0;
     __syncthreads();
-    for (int c0 = 0; c0 < n_k; c0 += NT) {
-      const int j = c0 + tid;
-      const bool f = (j < n_k) && flag[j] != 0;
-      const uint64_t bal = __ballot(f);
-      const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
-                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
-      if (lane == 0) wcount[wv] = __popcll(bal);
-      __syncthreads();
-      int before = 0, total = 0;
+    bool use = true;
 #pragma unroll
-      for (int x = 0; x < NWV; ++x) {
-        const int c = wcount[x];
-        before += (x < wv) ? c : 0;
-        total += c;
-      }
-      if (f) list[nb + before + below] = (uint16_t)j;
-      nb += total;
+    for (int x = 0; x < NWV; ++x) use = use && wcount[x] != 0;
+    if (use) {
+      nb = len;
+    } else {
+      uint8_t* const flag = reinterpret_cast<uint8_t*>(smem);
+      for (int j = tid; j < n_k; j += NT) flag[j] = 0;
       __syncthreads();
+      for (int64_t e = e0 + tid; e < e1; e += NT) {
+        const int j = col_idx[e];
+        if (j >= 0 && j < n_k) flag[j] = 1;
+      }
+      __syncthreads();
+      for (int c0 = 0; c0 < n_k; c0 += NT) {
+        const int j = c0 + tid;
+        const bool f = (j < n_k) && flag[j] != 0;
+        const uint64_t bal = __ballot(f);
+        const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
+        if (lane == 0) wcount[wv] = __popcll(bal);
+        __syncthreads();
+        int before = 0, total = 0;
+#pragma unroll
+        for (int x = 0; x < NWV; ++x) {
+          const int c = wcount[x];
+          before += (x < wv) ? c : 0;
+          total += c;
+        }
+        if (f) list[nb + before + below] = (uint16_t)j;
+        nb += total;
+        __syncthreads();
+      }
     }
     nb = __builtin_amdgcn_readfirstlane(nb);
   }
@@ -618,13 +641,15 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
     }
     // drain: P V of the last sub-tile S-1 (odd, so its probabilities are
     // pb[1]).  Its V slot was filled in sub-iteration S-3, one part by each
-    // wave, and the last barrier only covered loads up to S-4: every wave
-    // waits for all of its own loads (the later ones included, which nothing
-    // reads, so that none lands after the workgroup's LDS is handed on), then
-    // a barrier makes every wave's part visible.
-    wait_vm_barrier<0>();
+    // wave, and the last barrier only covered loads up to S-4, so one more
+    // wait and barrier make it visible.  The loads of the last two
+    // sub-iterations, which nothing reads, are waited out behind it: none may
+    // land once the rings serve the epilogue or the workgroup's LDS is handed
+    // on.
+    wait_vm_barrier<(R - 2) * 2 * C::LPW>();
     mfma_pair<D, BLK, BK, false, true>(ka, 0, qreg, sc[0], va, (uint32_t)(((S - 1) % R) * C::SUB),
                                    pb[1], oacc);
+    wait_vm_barrier<0>();
   }
 
   float l_tot = add_partner(l_run);
@@ -665,7 +690,15 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
   // ---- epilogue: O = O^T / l, lse -----------------------------------------
   const bool row_ok = (qrow < N) && (l_tot > 0.f);
   const float inv = row_ok ? 1.0f / l_tot : 0.f;
-  __bf16* orow = O + head + (size_t)qrow * D;
+  // O leaves through this wave's part of LDS (its own state's at two key
+  // splits, else of the K ring, which no wave reads any more), so that a store
+  // instruction writes whole rows; chunks are XOR-swizzled by 256-byte line.
+  // (8-byte stores straight from the accumulators, 32 rows an instruction: 14
+  // us more per call at 3,072 rows of 32 KiB.)
+  uint32_t el = lane;  // opaque, or the loop carries these addresses (0.8 % slower when dense)
+  launder(el);
+  const int er = el & 31, eg = el >> 5;
+  char* const ot = smem + w * (KSP == 2 ? C::DB * 4096 : 32 * C::KROW);
 #pragma unroll
   for (int db = 0; db < C::DB; ++db)
 #pragma unroll
@@ -673,9 +706,19 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
       f32x4_t v;
 #pragma unroll
       for (int u = 0; u < 4; ++u) v[u] = oacc[db][qd * 4 + u] * inv;
-      const int d0 = db * 32 + qd * 8 + g * 4;
-      *reinterpret_cast<bf16x4_t*>(orow + d0) = __builtin_convertvector(v, bf16x4_t);
+      *reinterpret_cast<bf16x4_t*>(ot + er * C::KROW +
+                                   (kswz<D, BLK, BK>(er, db * 4 + qd) << 4) + eg * 8) =
+          __builtin_convertvector(v, bf16x4_t);
     }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  char* const ob = reinterpret_cast<char*>(O + head + (size_t)(qb * BLK + w * 32) * D);
+#pragma unroll
+  for (int x = 0; x < C::SUB; x += 1024) {
+    const int row = (x + (int)el * 16) / C::KROW, c = ((int)el * 16 % C::KROW) >> 4;
+    *reinterpret_cast<f32x4_t*>(ob + x + el * 16) = *reinterpret_cast<const f32x4_t*>(
+        ot + row * C::KROW + (kswz<D, BLK, BK>(row, c) << 4));
+  }
   if (lse != nullptr && g == 0) {
     lse[(size_t)bh * n_pad + qrow] = row_ok ? (m_run + __log2f(l_tot)) * kLn2 : -INFINITY;
   }
