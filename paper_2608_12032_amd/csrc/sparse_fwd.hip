@@ -342,7 +342,6 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
   // per key split: K ring at smem, V ring at smem + RING; slot x at + x*SUB
   __shared__ __attribute__((aligned(1024))) char smem[KSP * 2 * C::RING];
   __shared__ uint16_t list[kMaxList];
-  __shared__ int wcount[NWV];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -393,6 +392,10 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
     // more per NT key blocks (with the epilogue's stores and the later wait
     // for unread loads: 255 -> 247 us at 3,072 rows of 7 blocks, 28.3 -> 26.5
     // at 156 rows of 12)
+    // (the waves' flags lie in the V slot that no load writes before the
+    // pipeline's first barrier: 8 bytes more LDS would cost d = 64 with 64-row
+    // blocks its fourth workgroup per CU, 41 against 31 us at 1,024 rows)
+    int* const wcount = reinterpret_cast<int*>(smem + C::RING + 2 * C::SUB);
     const int len = (int)(e1 - e0 < n_k ? e1 - e0 : n_k);
     bool sorted = e1 - e0 <= n_k;
     for (int x = tid; x < len; x += NT) {
@@ -733,6 +736,8 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
 // longest first (longest-processing-time-first list scheduling), so the tail
 // of the launch is made of short rows.  Ties keep the row order.  The order
 // changes only the schedule, never a result.
+// (Ranking the chunk in each workgroup instead of a kernel before it costs 2 us
+// per row in flight: 258 -> 266 us at 3,072 rows of 7 blocks.)
 constexpr int kOrderChunk = 128;
 
 // One workgroup per (chunk c = blockIdx.x, XCD x = blockIdx.y): the chunk's
@@ -810,8 +815,12 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, int B, int H,
   const int rows = BH * n_q;
   v = readable_v(v, o, (size_t)BH * n_pad * D * 2, workspace, stream);
   int* order = reinterpret_cast<int*>(static_cast<char*>(workspace) + order_offset(BH, n_pad, D));
-  if (KSP > 1) {
-    order = nullptr;  // every row starts at once
+  if (KSP > 1 || rows <= (BLK == 64 ? 512 : 384)) {
+    // every row starts at once (or nearly), and the order kernel would be most
+    // of what the order gains: 272 rows of 34 blocks 71 us with it, 74 without,
+    // of 4 blocks 32 / 24; 512 rows of 64 blocks 138 / 147, of 6 blocks 52 / 47;
+    // 64-row blocks, 512 rows of 64: 57 / 51
+    order = nullptr;
   } else {
     const int per_xcd = (rows + 7) / 8;
     hipLaunchKernelGGL(order_rows_kernel, dim3((per_xcd + kOrderChunk - 1) / kOrderChunk, 8),

@@ -100,3 +100,26 @@ def test_output_over_v(L, H, N):
         got = call(x)
         torch.cuda.synchronize()
         assert got.data_ptr() == x.data_ptr() and torch.equal(got, want)
+
+
+@pytest.mark.parametrize("H,Cq,Ck,N", [(48, 128, 128, 1000), (64, 64, 64, 500)])
+def test_order_rule(L, H, Cq, Ck, N):
+    """The largest call whose rows run in id order against the first H heads of
+    one head more, which gets a dispatch order: the same bits."""
+    d = 128
+    n_pad = O.padded_len(N, Cq, Ck)
+    n_q, n_k = n_pad // Cq, n_pad // Ck
+    print(f"[gpu-key-split] order rule: {H * n_q} rows", flush=True)
+    g = torch.Generator().manual_seed(90 + H)
+    q, k, v = (torch.randn((1, H + 1, n_pad, d), generator=g).bfloat16().cuda() for _ in range(3))
+    keep = torch.rand(((H + 1) * n_q, n_k), generator=g) < 0.5
+    rp = torch.zeros((H + 1) * n_q + 1, dtype=torch.int32)
+    rp[1:] = keep.sum(1).cumsum(0)
+    ci = keep.nonzero()[:, 1].int().cuda()
+    got = []
+    for h in (H, H + 1):
+        o, lse = L.losa_sparse_attn_fwd(*(x[:, :h].contiguous() for x in (q, k, v)), N, Cq, Ck,
+                                        rp[:h * n_q + 1].cuda(), ci, want_lse=True)
+        got.append((o[:, :H], lse[:, :H]))
+    torch.cuda.synchronize()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
