@@ -8,6 +8,7 @@ import instead of falling back to anything else.
 from __future__ import annotations
 
 import ctypes
+import functools
 import math
 import os
 
@@ -79,7 +80,7 @@ def _check(st: int, where: str):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -90,14 +91,20 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device) -> int:
+    """The current stream's handle, without building a torch.cuda.Stream."""
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _arg(t, name, device, dtype=None, shape=None, numel=None, nbytes=None):
     """Check a tensor argument before its pointer reaches the library, which
     sees raw device pointers and cannot tell a host tensor, a wrong element
     type or a short buffer from a valid one."""
+    # (a call makes up to eight of these: one expression for what is in order)
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.device == device and t.is_contiguous()
+            and (dtype is None or t.dtype == dtype) and (shape is None or t.shape == shape)
+            and (numel is None or t.numel() >= numel) and (nbytes is None or t.nbytes >= nbytes)):
+        return t
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if not t.is_cuda or t.device != device:
@@ -149,6 +156,10 @@ def workspace_bytes(which: int, dtype_code: int, B, H, N, d, block_q, block_k) -
     return int(lib.losa_workspace_bytes(which, dtype_code, B, H, N, d, block_q, block_k))
 
 
+# the same numbers, kept: a call with a workspace asks for its size each time
+_need = functools.lru_cache(maxsize=1024)(workspace_bytes)
+
+
 def losa_calibrate_mass(q, k, N: int, block_q: int, block_k: int | None = None,
                         scale: float | None = None, want_lse: bool = True, mass=None, lse=None,
                         workspace=None, two_sweep: bool = False):
@@ -176,7 +187,7 @@ def losa_calibrate_mass(q, k, N: int, block_q: int, block_k: int | None = None,
     if two_sweep or dcode != LOSA_DTYPE_BF16:
         workspace = None
     elif workspace is None:
-        need = workspace_bytes(0, dcode, B, H, N, d, block_q, block_k)
+        need = _need(0, dcode, B, H, N, d, block_q, block_k)
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
     if workspace is not None:
         _arg(workspace, "workspace", dev)
@@ -212,7 +223,7 @@ def losa_select_blocks(mass, N: int, block_q: int, block_k: int | None, tau: flo
     B, H, n_q, n_k = _mass_shape(mass, N, block_q, block_k)
     rows = B * H * n_q
     dev = mass.device
-    need = workspace_bytes(1, LOSA_DTYPE_F32, B, H, N, 1, block_q, block_k)
+    need = _need(1, LOSA_DTYPE_F32, B, H, N, 1, block_q, block_k)
     row_ptr, col_idx, workspace = _csr_out(row_ptr, col_idx, workspace, rows, n_k, dev, need)
     st = lib.losa_select_blocks(_ptr(mass), B, H, N, block_q, block_k, float(tau),
                                 _ptr(row_ptr), _ptr(col_idx), col_idx.numel(), _ptr(workspace),
@@ -228,7 +239,7 @@ def losa_select_blocks_topk(mass, N: int, block_q: int, block_k: int | None, k: 
     B, H, n_q, n_k = _mass_shape(mass, N, block_q, block_k)
     rows = B * H * n_q
     dev = mass.device
-    need = workspace_bytes(1, LOSA_DTYPE_F32, B, H, N, 1, block_q, block_k)
+    need = _need(1, LOSA_DTYPE_F32, B, H, N, 1, block_q, block_k)
     row_ptr, col_idx, workspace = _csr_out(row_ptr, col_idx, workspace, rows, n_k, dev, need)
     st = lib.losa_select_blocks_topk(_ptr(mass), B, H, N, block_q, block_k, int(k),
                                      _ptr(row_ptr), _ptr(col_idx), col_idx.numel(),
@@ -248,7 +259,7 @@ def losa_block_recall(mass, N: int, block_q: int, block_k: int | None, row_ptr, 
     _arg(col_idx, "col_idx", dev, dtype=torch.int32)
     rec_rows = torch.empty(B * H * n_q, dtype=torch.float32, device=dev) if want_rows else None
     rec_heads = torch.empty((B, H), dtype=torch.float32, device=dev) if want_heads else None
-    need = workspace_bytes(3, LOSA_DTYPE_F32, B, H, N, 1, block_q, block_k)
+    need = _need(3, LOSA_DTYPE_F32, B, H, N, 1, block_q, block_k)
     if workspace is None:
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
     _arg(workspace, "workspace", dev, nbytes=need)
@@ -281,7 +292,7 @@ def losa_sparse_attn_fwd(q, k, v, N: int, block_q: int, block_k: int | None, row
         lse = torch.empty((B, H, Np), dtype=torch.float32, device=dev)
     if want_lse:
         _arg(lse, "lse", dev, dtype=torch.float32, shape=(B, H, Np))
-    need = workspace_bytes(2, dcode, B, H, N, d, block_q, block_k)
+    need = _need(2, dcode, B, H, N, d, block_q, block_k)
     if workspace is None and need > 0:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
     if workspace is not None:
@@ -344,7 +355,7 @@ def losa_construct(q, k, v, N: int, block_q: int, block_k: int | None = None,
         lse = None
     if lse is not None:
         _arg(lse, "lse", dev, dtype=torch.float32, shape=(B, H, Np))
-    need = workspace_bytes(4, dcode, B, H, N, d, block_q, block_k)
+    need = _need(4, dcode, B, H, N, d, block_q, block_k)
     if workspace is None and need > 0:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
     if workspace is not None:
