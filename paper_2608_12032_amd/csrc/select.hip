@@ -30,6 +30,8 @@
 // (1.8 TB/s), where a bitonic sort of each row's 4,096 keys in LDS took 2,314
 // us of barrier steps; compact_rows 33 us (110 us from byte flags), scan_counts
 // 7 us (29 us with one row per load).
+#include <type_traits>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -69,6 +71,21 @@ __device__ __forceinline__ T wave_total(T v) {
   v = val(r[0]) + val(r[1]);
   r = __builtin_amdgcn_permlane32_swap(bits(v), bits(v), false, false);
   return val(r[0]) + val(r[1]);
+}
+
+// Maximum over the wave, the same in every lane.
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  auto dpp = [](uint32_t x, auto ctrl) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, 0xf, 0xf, false);
+  };
+  v = max(v, dpp(v, std::integral_constant<int, 0x128>{}));  // row_ror:8
+  v = max(v, dpp(v, std::integral_constant<int, 0x124>{}));
+  v = max(v, dpp(v, std::integral_constant<int, 0x122>{}));
+  v = max(v, dpp(v, std::integral_constant<int, 0x121>{}));
+  auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = max((uint32_t)r[0], (uint32_t)r[1]);
+  r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return __builtin_amdgcn_readfirstlane(max((uint32_t)r[0], (uint32_t)r[1]));
 }
 
 __device__ __forceinline__ uint64_t read_lane(uint64_t x, int y) {
@@ -144,16 +161,34 @@ __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 
     };
     auto reached = [&](uint32_t c) -> bool {
       if constexpr (!TOPK) {
-        float s = 0.f;
+        float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int u = 0; u < V; ++u) s += bits[u] >= c ? __uint_as_float(bits[u]) : 0.f;
-        const float d = wave_total(s) - tau;
-        // V + 6 additions: within 2^-17 of the sum
-        static_assert(V + 6 <= 1 << 7, "rounding error of the fp32 sum");
-        if (!(fabsf(d) <= tau * 0x1p-17f)) return __builtin_amdgcn_readfirstlane(d > 0.f);
+        for (int u = 0; u < V; ++u) s[u & 3] += bits[u] >= c ? __uint_as_float(bits[u]) : 0.f;
+        const float d = wave_total((s[0] + s[1]) + (s[2] + s[3])) - tau;
+        // V/4 + 8 additions deep: within 2^-19 of the sum
+        static_assert(V / 4 + 8 <= 1 << 5, "rounding error of the fp32 sum");
+        if (!(fabsf(d) <= tau * 0x1p-19f)) return __builtin_amdgcn_readfirstlane(d > 0.f);
       }
       return weight_from(c) >= target;
     };
+    // Bounds that settle a step without a pass over the blocks: nothing weighs
+    // in at more than the heaviest mass, and the blocks below c weigh less than
+    // n_k c together (the fp32 total is within 2^-17 of the exact one; a
+    // mass over 1 counts as 1: then neither bound is used).
+    uint32_t top = 0x7fffffffu;
+    float spare = 0.f;  // weight that can be left out for certain, per block
+    if constexpr (!TOPK) {
+      float sum = 0.f;
+      top = 0;
+#pragma unroll
+      for (int u = 0; u < V; ++u) {
+        sum += __uint_as_float(bits[u]);
+        top = max(top, bits[u]);
+      }
+      top = wave_max(top);
+      sum = wave_total(sum);
+      spare = top <= 0x3f800000u ? (sum * (1.f - 0x1p-16f) - tau) / (float)n_k : 0.f;
+    }
     uint32_t T = 0;
     int shift = 31;      // T's bits from here up are settled
     // whether block u of this lane shares them (threshold rule: a block of
@@ -167,7 +202,9 @@ __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 
       const int stop = shift == 31 ? 18 : (shift == 18 ? 9 : 0);
       while (shift > stop) {
         --shift;
-        if (reached(T | 1u << shift)) T |= 1u << shift;
+        const uint32_t c = T | 1u << shift;
+        if (c > top) continue;
+        if (__uint_as_float(c) < spare || reached(c)) T = c;
       }
       if (!TOPK && T == 0 && !reached(1)) {  // the row never reaches tau
         all = true;
@@ -359,6 +396,7 @@ hipError_t launch_select(const float* mass, int B, int H, int N, int block_q, in
   if (n_k <= 64) launch_sel<1>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks, stream);
   else if (n_k <= 256) launch_sel<4>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks, stream);
   else if (n_k <= 1024) launch_sel<16>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks, stream);
+  else if (n_k <= 2048) launch_sel<32>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks, stream);
   else if (n_k <= 4096) launch_sel<64>(mass, rows, n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks, stream);
   else return hipErrorInvalidValue;
   hipError_t err = hipGetLastError();
