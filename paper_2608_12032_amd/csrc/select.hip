@@ -26,8 +26,8 @@
 // rounding error of tau.
 //
 // Bound: the search's compare, select and add per block and step, and reading
-// the masses.  At 22,296 rows of 3,716 masses (331 MB): select_rows 180 us
-// (1.8 TB/s), where a bitonic sort of each row's 4,096 keys in LDS took 2,314
+// the masses.  At 22,296 rows of 3,716 masses (331 MB): select_rows 163 us
+// (2.0 TB/s), where a bitonic sort of each row's 4,096 keys in LDS took 2,314
 // us of barrier steps; compact_rows 33 us (110 us from byte flags), scan_counts
 // 7 us (29 us with one row per load).
 #include <type_traits>

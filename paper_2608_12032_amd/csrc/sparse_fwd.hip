@@ -4,7 +4,7 @@
 // Work unit.  One workgroup owns one CSR row r = (b*H + h)*n_q + i: the BLK
 // query rows of query block i, 32 per wave (BLK/32 waves, one per SIMD for
 // BLK = 128), and walks only the key blocks the row retains.  Two workgroups
-// share a CU at d = 128 and three at d = 64, so each SIMD runs two or three
+// share a CU at d = 128 and four at d = 64, so each SIMD runs two or four
 // independent waves: while one waits at its workgroup barrier or on its
 // exponentials, another keeps the matrix core busy.  The workgroup first
 // turns its CSR entries into a sorted list of distinct valid block ids in LDS
@@ -104,7 +104,7 @@ struct FwdCfg {
   static constexpr int DB = D / 32;                  // 32-row d sub-blocks of O^T
   static constexpr int NS = BK / 32;                 // 32-key sub-tiles per key block
   static constexpr int R = kRing;                    // slots per ring
-  static constexpr int LEAD = D == 64 ? 4 : 2;       // MFMAs an LDS operand read leads by
+  static constexpr int LEAD = 2;                     // MFMAs an LDS operand read leads by
   static constexpr int BPI = R / NS;                 // key blocks per unrolled loop pass
   static constexpr int SUB = 32 * D * 2;             // bytes of a K or V sub-tile
   static constexpr int RING = R * SUB;               // bytes of one ring
@@ -315,13 +315,14 @@ constexpr float kSumBound = 1048576.0f;
 
 // Waves per SIMD the register budget is cut for.  128-row query blocks: two at
 // d = 128 (output accumulators, Q operands and two score tiles take ~250
-// registers); three at d = 64, where a wave's VALU work per MFMA is twice that
-// of d = 128 and a third wave hides more of it (168 registers; the rings and
-// block list, 40 KiB per workgroup, allow four).  64-row blocks are limited by
-// LDS instead.
+// registers); four at d = 64, where a wave's VALU work per MFMA is twice that
+// of d = 128 and more waves hide more of it (128 registers, three of them
+// spilled outside the loop; the rings and block list, 40 KiB per workgroup,
+// allow four).  Against three waves at the CogVideoX shape: 3,004 -> 2,975 us,
+// 3,051 -> 2,953 with 32-key blocks.  64-row blocks are limited by LDS instead.
 template <int D, int BLK>
 constexpr int fwd_waves_per_simd() {
-  return BLK == 128 ? (D == 64 ? 3 : 2) : 1;
+  return BLK == 128 ? (D == 64 ? 4 : 2) : 1;
 }
 
 template <int D, int BLK, int BK, bool DENSE, int KSP>
