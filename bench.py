@@ -140,7 +140,7 @@ def measured_traffic(workload: str):
 # one sweep with block statistics).
 KERNELS = {"sparse_fwd": ("sparse_fwd_bf16_kernel", "Lb0E"),
            "dense_fwd": ("sparse_fwd_bf16_kernel", "Lb1E"),
-           "transpose_v": ("transpose_v_kernel",), "calibrate": ("calib_bf16_kernel", "true>"),
+           "calibrate": ("calib_bf16_kernel", "true>"),
            "stat_mass": ("stat_mass_kernel",),
            "calibrate_two_sweep": ("calib_bf16_kernel", "false>"),
            "select_rows": ("select_rows_kernel",), "compact_rows": ("compact_rows_kernel",)}
