@@ -316,18 +316,19 @@ constexpr float kSumBound = 1048576.0f;
 // Waves per SIMD the register budget is cut for.  128-row query blocks: two at
 // d = 128 (output accumulators, Q operands and two score tiles take ~250
 // registers); four at d = 64, where a wave's VALU work per MFMA is twice that
-// of d = 128 and more waves hide more of it (128 registers, three of them
-// spilled outside the loop; the rings and block list, 40 KiB per workgroup,
-// allow four).  Against three waves at the CogVideoX shape: 3,004 -> 2,975 us,
+// of d = 128 and more waves hide more of it (128 registers; the rings and
+// block list, 40 KiB per workgroup, allow four).  Against three waves at the CogVideoX shape: 3,004 -> 2,975 us,
 // 3,051 -> 2,953 with 32-key blocks.  64-row blocks are limited by LDS instead.
-template <int D, int BLK>
+// (Dense with 32-key blocks keeps three waves: it also stores a statistic per
+// sub-tile, and at 128 registers one would spill.)
+template <int D, int BLK, int BK, bool DENSE>
 constexpr int fwd_waves_per_simd() {
-  return BLK == 128 ? (D == 64 ? 4 : 2) : 1;
+  return BLK == 128 ? (D == 64 ? (DENSE && BK == 32 ? 3 : 4) : 2) : 1;
 }
 
 template <int D, int BLK, int BK, bool DENSE, int KSP>
 __global__ void __launch_bounds__(BLK * 2 * KSP)
-    __attribute__((amdgpu_waves_per_eu(KSP == 1 ? fwd_waves_per_simd<D, BLK>() : BLK / 64)))
+    __attribute__((amdgpu_waves_per_eu(KSP == 1 ? fwd_waves_per_simd<D, BLK, BK, DENSE>() : BLK / 64)))
     sparse_fwd_bf16_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K,
                            const __bf16* __restrict__ V, const int32_t* __restrict__ row_ptr,
                            const int32_t* __restrict__ col_idx, int64_t col_len,
@@ -692,16 +693,21 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
   }
 
   // ---- epilogue: O = O^T / l, lse -----------------------------------------
-  const bool row_ok = (qrow < N) && (l_tot > 0.f);
+  // The lane is counted anew here, behind an opaque zero: a loop that carries it,
+  // the query row or the addresses below spills at d = 64 and was 0.8 % slower
+  // when dense.
+  uint32_t el = 0;
+  launder(el);
+  el = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, el));
+  const int er = el & 31, eg = el >> 5;
+  const int erow = qb * BLK + w * 32 + er;
+  const bool row_ok = (erow < N) && (l_tot > 0.f);
   const float inv = row_ok ? 1.0f / l_tot : 0.f;
   // O leaves through this wave's part of LDS (its own state's at two key
   // splits, else of the K ring, which no wave reads any more), so that a store
   // instruction writes whole rows; chunks are XOR-swizzled by 256-byte line.
   // (8-byte stores straight from the accumulators, 32 rows an instruction: 14
   // us more per call at 3,072 rows of 32 KiB.)
-  uint32_t el = lane;  // opaque, or the loop carries these addresses (0.8 % slower when dense)
-  launder(el);
-  const int er = el & 31, eg = el >> 5;
   char* const ot = smem + w * (KSP == 2 ? C::DB * 4096 : 32 * C::KROW);
 #pragma unroll
   for (int db = 0; db < C::DB; ++db)
@@ -723,8 +729,8 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
     *reinterpret_cast<f32x4_t*>(ob + x + el * 16) = *reinterpret_cast<const f32x4_t*>(
         ot + row * C::KROW + (kswz<D, BLK, BK>(row, c) << 4));
   }
-  if (lse != nullptr && g == 0) {
-    lse[(size_t)bh * n_pad + qrow] = row_ok ? (m_run + __log2f(l_tot)) * kLn2 : -INFINITY;
+  if (lse != nullptr && eg == 0) {
+    lse[(size_t)bh * n_pad + erow] = row_ok ? (m_run + __log2f(l_tot)) * kLn2 : -INFINITY;
   }
 }
 
