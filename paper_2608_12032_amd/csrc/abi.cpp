@@ -408,7 +408,7 @@ losa_status losa_construct(const void* q, const void* k, const void* v, losa_dty
                                             static_cast<const char*>(k) + off,
                                             static_cast<const char*>(v) + off, 1, g, N, s.n_pad,
                                             scale, static_cast<char*>(o) + off, l, stat,
-                                            ws + L.fwd, s.rows, hs),
+                                            ws + L.fwd, hs),
                     "losa_construct (dense attention)");
     if (st != LOSA_OK) return st;
     st = hip_status(losa::launch_stat_mass(block_q, block_k, stat, l, g, N, s.n_pad,

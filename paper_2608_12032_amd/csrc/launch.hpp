@@ -53,11 +53,9 @@ hipError_t launch_sparse_fwd_bf16(int d, int blk, int blk_k, const void* q, cons
                                   hipStream_t stream);
 // dense attention over every valid key (row_ptr == nullptr for the f32 path)
 // stat != nullptr: also the block statistics [B*H][n_k][n_pad] (log2 units)
-// call_rows: query blocks of the whole call, of which this may be a part
 hipError_t launch_dense_bf16(int d, int blk, int blk_k, const void* q, const void* k,
                              const void* v, int B, int H, int N, int n_pad, float scale, void* o,
-                             float* lse, float* stat, void* workspace, int64_t call_rows,
-                             hipStream_t stream);
+                             float* lse, float* stat, void* workspace, hipStream_t stream);
 hipError_t launch_sparse_fwd_f32(int d, int blk, int blk_k, const void* q, const void* k,
                                  const void* v, int B, int H, int N, int n_pad, float scale,
                                  const int32_t* row_ptr, const int32_t* col_idx, int64_t col_len,

@@ -326,9 +326,9 @@ constexpr int fwd_waves_per_simd() {
   return BLK == 128 ? (D == 64 ? (DENSE && BK == 32 ? 3 : 4) : 2) : 1;
 }
 
-template <int D, int BLK, int BK, bool DENSE, int KSP>
-__global__ void __launch_bounds__(BLK * 2 * KSP)
-    __attribute__((amdgpu_waves_per_eu(KSP == 1 ? fwd_waves_per_simd<D, BLK, BK, DENSE>() : BLK / 64)))
+template <int D, int BLK, int BK, bool DENSE>
+__global__ void __launch_bounds__(BLK * 2)
+    __attribute__((amdgpu_waves_per_eu(fwd_waves_per_simd<D, BLK, BK, DENSE>())))
     sparse_fwd_bf16_kernel(const __bf16* __restrict__ Q, const __bf16* __restrict__ K,
                            const __bf16* __restrict__ V, const int32_t* __restrict__ row_ptr,
                            const int32_t* __restrict__ col_idx, int64_t col_len,
@@ -339,17 +339,14 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
   constexpr int NS = C::NS;
   constexpr int R = C::R;
   constexpr int BPI = C::BPI;
-  constexpr int NT = C::NT * KSP;
-  constexpr int NWV = C::NW * KSP;
-  // per key split: K ring at smem, V ring at smem + RING; slot x at + x*SUB
-  __shared__ __attribute__((aligned(1024))) char smem[KSP * 2 * C::RING];
+  constexpr int NT = C::NT;
+  // K ring at smem, V ring at smem + RING; slot x at + x*SUB
+  __shared__ __attribute__((aligned(1024))) char smem[2 * C::RING];
   __shared__ uint16_t list[kMaxList];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int w = KSP == 1 ? wv : wv % C::NW;   // 32-row group
-  const int sp = KSP == 1 ? 0 : wv / C::NW;   // key split
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31;
   const int g = lane >> 5;
 
@@ -406,12 +403,12 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
       sorted = sorted && j > before && j < n_k;
       list[x] = (uint16_t)j;
     }
-    if (lane == 0) wcount[wv] = 1;
-    if (!sorted) wcount[wv] = 0;
+    if (lane == 0) wcount[w] = 1;
+    if (!sorted) wcount[w] = 0;
     __syncthreads();
     bool use = true;
 #pragma unroll
-    for (int x = 0; x < NWV; ++x) use = use && wcount[x] != 0;
+    for (int x = 0; x < C::NW; ++x) use = use && wcount[x] != 0;
     if (use) {
       nb = len;
     } else {
@@ -429,13 +426,13 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
         const uint64_t bal = __ballot(f);
         const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
-        if (lane == 0) wcount[wv] = __popcll(bal);
+        if (lane == 0) wcount[w] = __popcll(bal);
         __syncthreads();
         int before = 0, total = 0;
 #pragma unroll
-        for (int x = 0; x < NWV; ++x) {
+        for (int x = 0; x < C::NW; ++x) {
           const int c = wcount[x];
-          before += (x < wv) ? c : 0;
+          before += (x < w) ? c : 0;
           total += c;
         }
         if (f) list[nb + before + below] = (uint16_t)j;
@@ -449,16 +446,12 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
   // stream is padded to whole loop passes with sub-tiles whose keys are all
   // masked (they add nothing to O or l); larger blocks fill passes exactly,
   // or leave half a pass that the loop stops after.
-  // A key split takes its half of the list; both run the trips of the longer.
-  const int nb_trip = KSP == 1 ? nb : (nb + KSP - 1) / KSP;
-  const int nb0 = sp * nb_trip;
-  const int S_real = KSP == 1 ? nb * NS : max(0, min(nb_trip, nb - nb0)) * NS;
-  const int S = (NS == 1) ? (nb_trip + R - 1) / R * R : nb_trip * NS;
+  const int S_real = nb * NS;
+  const int S = (NS == 1) ? (nb + R - 1) / R * R : S_real;
 
   // per-lane LDS addresses of the operand reads in K slot 0 / V slot 0; the
   // slot, and for V the key step and the d block, are immediates
-  char* const ring = smem + sp * 2 * C::RING;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
   uint32_t ka[C::KS];
 #pragma unroll
   for (int st = 0; st < C::KS; ++st)
@@ -499,7 +492,7 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
   };
   // list entry x as a scalar, clamped into the list
   auto block_at = [&](int x) -> int {
-    return __builtin_amdgcn_readfirstlane((int)list[nb0 + x < nb ? nb0 + x : nb - 1]);
+    return __builtin_amdgcn_readfirstlane((int)list[x < nb ? x : nb - 1]);
   };
 
   f32x16_t oacc[C::DB];
@@ -528,8 +521,8 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
       load_k(y, jy, y % NS);
       if (y < R - 2) load_v(y, jy, y % NS);
     }
-    for (int x = (w * 64 + lane) * 16; x < C::SUB; x += C::NT * 16)
-      *reinterpret_cast<f32x4_t*>(ring + C::RING + (R - 1) * C::SUB + x) = f32x4_t{};
+    for (int x = tid * 16; x < C::SUB; x += NT * 16)
+      *reinterpret_cast<f32x4_t*>(smem + C::RING + (R - 1) * C::SUB + x) = f32x4_t{};
 #pragma unroll
     for (int a2 = 0; a2 < 2; ++a2)
 #pragma unroll
@@ -627,7 +620,7 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
       int jf[BPI];
 #pragma unroll
       for (int x = 0; x < BPI; ++x) {
-        const int xi = nb0 + (u + 2) * BPI + x;
+        const int xi = (u + 2) * BPI + x;
         jf[x] = (int)list[xi < nb ? xi : nb - 1];
       }
       sub_iter(I0{}, u);
@@ -657,40 +650,7 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
     wait_vm_barrier<0>();
   }
 
-  float l_tot = add_partner(l_run);
-  if constexpr (KSP == 2) {
-    // the second half's state goes through LDS (the rings are done with) and
-    // the first half's waves merge it: common max, sums and outputs rescaled
-    f32x4_t* const po = reinterpret_cast<f32x4_t*>(smem) + w * (C::DB * 4 * 64) + lane;
-    float* const ml = reinterpret_cast<float*>(smem + C::NW * C::DB * 4096) + w * 128 + lane;
-    static_assert(C::NW * (C::DB * 4096 + 512) <= KSP * 2 * C::RING, "states fit the rings");
-    __syncthreads();
-    if (sp == 1) {
-      ml[0] = m_run;
-      ml[64] = l_tot;
-#pragma unroll
-      for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          po[(db * 4 + e) * 64] = f32x4_t{oacc[db][4 * e], oacc[db][4 * e + 1],
-                                          oacc[db][4 * e + 2], oacc[db][4 * e + 3]};
-    }
-    __syncthreads();
-    if (sp == 1) return;
-    const float m1 = ml[0];
-    const float m_new = fmaxf(m_run, m1);
-    const float a0 = fast_exp2(m_run - m_new), a1 = fast_exp2(m1 - m_new);
-    m_run = m_new;
-    l_tot = l_tot * a0 + ml[64] * a1;
-#pragma unroll
-    for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const f32x4_t p = po[(db * 4 + e) * 64];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) oacc[db][4 * e + u] = oacc[db][4 * e + u] * a0 + p[u] * a1;
-      }
-  }
+  const float l_tot = add_partner(l_run);
 
   // ---- epilogue: O = O^T / l, lse -----------------------------------------
   // The lane is counted anew here, behind an opaque zero: a loop that carries it,
@@ -703,12 +663,11 @@ __global__ void __launch_bounds__(BLK * 2 * KSP)
   const int erow = qb * BLK + w * 32 + er;
   const bool row_ok = (erow < N) && (l_tot > 0.f);
   const float inv = row_ok ? 1.0f / l_tot : 0.f;
-  // O leaves through this wave's part of LDS (its own state's at two key
-  // splits, else of the K ring, which no wave reads any more), so that a store
-  // instruction writes whole rows; chunks are XOR-swizzled by 256-byte line.
+  // O leaves through this wave's part of the K ring, which no wave reads any
+  // more, so that a store instruction writes whole rows; chunks are XOR-swizzled by 256-byte line.
   // (8-byte stores straight from the accumulators, 32 rows an instruction: 14
   // us more per call at 3,072 rows of 32 KiB.)
-  char* const ot = smem + w * (KSP == 2 ? C::DB * 4096 : 32 * C::KROW);
+  char* const ot = smem + w * 32 * C::KROW;
 #pragma unroll
   for (int db = 0; db < C::DB; ++db)
 #pragma unroll
@@ -800,19 +759,7 @@ const void* readable_v(const void* v, const void* o, size_t bytes, void* room,
   return room;
 }
 
-// Two key splits per row where a call's rows leave CUs with one workgroup or
-// none: a wave alone on its SIMD waits out its own exponentials and barriers.
-// Full rows, one split against two: 256 rows 91.0 / 81.5 us (d = 128, 128-row
-// blocks), 59.2 / 48.6 (d = 64), 42.2 / 29.8 (d = 128, 64-row blocks); 320 rows
-// 136.8 / 152.6, 89.6 / 97.7, 54.4 / 57.2.  With 64-row blocks at d = 64 two
-// split workgroups fit a CU: 79.8 / 54.1 at 512 rows, 103 / 92 at 640 (59 / 60
-// with half the blocks kept).  Under 512 keys the merge costs more than half
-// the stream: 12.9 / 14.4 us at 128 keys.
-inline bool split_keys(int d, int blk, int64_t rows, int n_pad) {
-  return rows <= (d == 64 && blk == 64 ? 512 : 256) && n_pad >= 512;
-}
-
-template <int D, int BLK, int BK, int KSP>
+template <int D, int BLK, int BK>
 hipError_t launch_fwd(const void* q, const void* k, const void* v, int B, int H, int N, int n_pad,
                       float scale, const int32_t* row_ptr, const int32_t* col_idx,
                       int64_t col_len, void* o, float* lse, void* workspace, hipStream_t stream) {
@@ -822,7 +769,7 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, int B, int H,
   const int rows = BH * n_q;
   v = readable_v(v, o, (size_t)BH * n_pad * D * 2, workspace, stream);
   int* order = reinterpret_cast<int*>(static_cast<char*>(workspace) + order_offset(BH, n_pad, D));
-  if (KSP > 1 || rows <= (BLK == 64 ? 512 : 384)) {
+  if (rows <= (BLK == 64 ? 512 : 384)) {
     // every row starts at once (or nearly), and the order kernel would be most
     // of what the order gains: 272 rows of 34 blocks 71 us with it, 74 without,
     // of 4 blocks 32 / 24; 512 rows of 64 blocks 138 / 147, of 6 blocks 52 / 47;
@@ -833,8 +780,8 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, int B, int H,
     hipLaunchKernelGGL(order_rows_kernel, dim3((per_xcd + kOrderChunk - 1) / kOrderChunk, 8),
                        dim3(kOrderChunk), 0, stream, row_ptr, col_len, rows, n_k, order);
   }
-  hipLaunchKernelGGL((sparse_fwd_bf16_kernel<D, BLK, BK, false, KSP>), dim3(rows),
-                     dim3(FwdCfg<D, BLK, BK>::NT * KSP), 0, stream, static_cast<const __bf16*>(q),
+  hipLaunchKernelGGL((sparse_fwd_bf16_kernel<D, BLK, BK, false>), dim3(rows),
+                     dim3(FwdCfg<D, BLK, BK>::NT), 0, stream, static_cast<const __bf16*>(q),
                      static_cast<const __bf16*>(k), static_cast<const __bf16*>(v), row_ptr,
                      col_idx, col_len, static_cast<__bf16*>(o), lse, nullptr, order, n_q, n_k, N,
                      n_pad, scale * kLog2e);
@@ -844,7 +791,7 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, int B, int H,
 // Dense attention of every query block over every valid key (the forward
 // kernel with full rows): O, lse and, if stat is given, the block statistics
 // of the construction step.
-template <int D, int BLK, int BK, int KSP>
+template <int D, int BLK, int BK>
 hipError_t launch_dense(const void* q, const void* k, const void* v, int B, int H, int N,
                         int n_pad, float scale, void* o, float* lse, float* stat, void* workspace,
                         hipStream_t stream) {
@@ -853,8 +800,8 @@ hipError_t launch_dense(const void* q, const void* k, const void* v, int B, int 
   const int n_q = n_pad / BLK;
   const int n_k = n_pad / BK;
   const int rows = BH * n_q;
-  hipLaunchKernelGGL((sparse_fwd_bf16_kernel<D, BLK, BK, true, KSP>), dim3(rows),
-                     dim3(FwdCfg<D, BLK, BK>::NT * KSP), 0, stream, static_cast<const __bf16*>(q),
+  hipLaunchKernelGGL((sparse_fwd_bf16_kernel<D, BLK, BK, true>), dim3(rows),
+                     dim3(FwdCfg<D, BLK, BK>::NT), 0, stream, static_cast<const __bf16*>(q),
                      static_cast<const __bf16*>(k), static_cast<const __bf16*>(v), nullptr,
                      nullptr, 0, static_cast<__bf16*>(o), lse, stat, nullptr, n_q, n_k, N, n_pad,
                      scale * kLog2e);
@@ -868,13 +815,10 @@ hipError_t launch_sparse_fwd_bf16(int d, int blk, int blk_k, const void* q, cons
                                   const int32_t* row_ptr, const int32_t* col_idx,
                                   int64_t col_len, void* o, float* lse, void* workspace,
                                   hipStream_t stream) {
-  const bool split = split_keys(d, blk, (int64_t)B * H * (n_pad / blk), n_pad);
-#define LOSA_FWD(DD, BB, KK)                                                                 \
-  if (d == DD && blk == BB && blk_k == KK)                                                   \
-    return split ? launch_fwd<DD, BB, KK, 2>(q, k, v, B, H, N, n_pad, scale, row_ptr, col_idx, \
-                                             col_len, o, lse, workspace, stream)             \
-                 : launch_fwd<DD, BB, KK, 1>(q, k, v, B, H, N, n_pad, scale, row_ptr, col_idx, \
-                                             col_len, o, lse, workspace, stream);
+#define LOSA_FWD(DD, BB, KK)                                                               \
+  if (d == DD && blk == BB && blk_k == KK)                                                 \
+    return launch_fwd<DD, BB, KK>(q, k, v, B, H, N, n_pad, scale, row_ptr, col_idx, col_len, o, \
+                                  lse, workspace, stream);
   LOSA_FWD(128, 128, 128)
   LOSA_FWD(64, 128, 128)
   LOSA_FWD(128, 64, 64)
@@ -889,17 +833,11 @@ hipError_t launch_sparse_fwd_bf16(int d, int blk, int blk_k, const void* q, cons
 
 hipError_t launch_dense_bf16(int d, int blk, int blk_k, const void* q, const void* k,
                              const void* v, int B, int H, int N, int n_pad, float scale, void* o,
-                             float* lse, float* stat, void* workspace, int64_t call_rows,
-                             hipStream_t stream) {
-  // by the whole call's rows: its groups of heads, and the sparse forward over
-  // the same shape, then split alike and give the same bits
-  const bool split = split_keys(d, blk, call_rows, n_pad);
-#define LOSA_DENSE(DD, BB, KK)                                                                \
-  if (d == DD && blk == BB && blk_k == KK)                                                    \
-    return split ? launch_dense<DD, BB, KK, 2>(q, k, v, B, H, N, n_pad, scale, o, lse, stat,  \
-                                               workspace, stream)                             \
-                 : launch_dense<DD, BB, KK, 1>(q, k, v, B, H, N, n_pad, scale, o, lse, stat,  \
-                                               workspace, stream);
+                             float* lse, float* stat, void* workspace, hipStream_t stream) {
+#define LOSA_DENSE(DD, BB, KK)                                                              \
+  if (d == DD && blk == BB && blk_k == KK)                                                  \
+    return launch_dense<DD, BB, KK>(q, k, v, B, H, N, n_pad, scale, o, lse, stat, workspace, \
+                                    stream);
   LOSA_DENSE(128, 128, 128)
   LOSA_DENSE(64, 128, 128)
   LOSA_DENSE(128, 64, 64)

@@ -1,9 +1,9 @@
-"""bf16 forward on both sides of its key-split rule: calls of few query blocks
-give each row two wave groups that take half of its key blocks and merge.
+"""bf16 forward in calls of few and of many query blocks (fewer and more than the
+GPU's CUs, and both sides of the rule that gives a call a row order).
 Rows with no, one, an odd and an even number of blocks, repeated and stray ids,
-32-key blocks that do not fill the pipeline's passes, a ragged last block in
-either half; the construction step equals the sparse forward over a full
-support bitwise on both sides.  Bars: the bf16 path's."""
+32-key blocks that do not fill the pipeline's passes, a ragged last block; the
+construction step equals the sparse forward over a full support bitwise,
+whether its heads are worked through together or one at a time.  Bars: the bf16 path's."""
 import numpy as np
 import pytest
 import torch
@@ -12,8 +12,8 @@ from oracle import losa_oracle as O
 
 pytestmark = pytest.mark.gpu
 
-# (heads, d, block_q, block_k, N): split at most 256 rows (512 at d = 64 with
-# 64-row blocks) and at least 512 padded keys
+# (heads, d, block_q, block_k, N): a few rows, and just below and above 256 (512
+# at d = 64 with 64-row blocks), at fewer and more than 512 padded keys
 CASES = [(2, 128, 128, 128, 385), (2, 128, 128, 128, 384), (51, 128, 128, 128, 577),
          (52, 128, 128, 128, 577), (51, 64, 128, 128, 600), (52, 64, 128, 128, 600),
          (2, 128, 128, 32, 490), (52, 64, 128, 32, 530), (28, 128, 64, 64, 570),
@@ -83,7 +83,7 @@ def test_key_split(L, case):
     assert np.abs(f64(mass[:, :2]) - m_ref).max() <= 1e-4
 
 
-@pytest.mark.parametrize("H,N", [(2, 600), (40, 1000)])   # split and not
+@pytest.mark.parametrize("H,N", [(2, 600), (40, 1000)])   # few rows and many
 def test_output_over_v(L, H, N):
     """o written over v gives what separate buffers give, in both calls."""
     n_pad = O.padded_len(N, 128, 128)
