@@ -204,19 +204,14 @@ __device__ __forceinline__ float tile_exp(typename F32Acc<M>::type* s, float m) 
   return part;
 }
 
-// The row's distinct valid key blocks, ascending, into list (dense: every
-// block holding a valid key); returns their count.  flag and wcount are LDS
-// scratch.  All NT threads call it.
+// The row's distinct valid key blocks, ascending, into list; returns their
+// count.  flag and wcount are LDS scratch; n_k <= kSparseFwdMaxNk, which flag and
+// list have room for.  All NT threads call it.
 template <int NT>
-__device__ int block_list(int dense, int n_kv, int n_k, const int32_t* __restrict__ row_ptr,
+__device__ int block_list(int n_k, const int32_t* __restrict__ row_ptr,
                           const int32_t* __restrict__ col_idx, int64_t col_len, int r,
                           uint8_t* flag, uint16_t* list, int* wcount) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (dense) {
-    for (int j = tid; j < n_kv; j += NT) list[j] = (uint16_t)j;
-    __syncthreads();
-    return n_kv;
-  }
   for (int j = tid; j < n_k; j += NT) flag[j] = 0;
   __syncthreads();
   int64_t e0 = row_ptr[r], e1 = row_ptr[r + 1];
@@ -252,7 +247,9 @@ constexpr int kF32Waves = 8;  // waves of a workgroup (key splits): two per SIMD
 
 // Attention of M query rows over their query block's key blocks (bk_sub
 // 32-key sub-tiles each).  PV: O and, if given, lse (natural log).  !PV: only
-// the normaliser, in log2 units, to lse (dense).
+// the normaliser, in log2 units, to lse (dense).  Dense: every sub-tile that
+// holds a valid key, in order and from no list, so that no number of key blocks
+// is too large (the calibration takes any).
 template <int D, int M, bool PV>
 __global__ void __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(2)))
     attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
@@ -287,11 +284,12 @@ __global__ void __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_pe
   f32x4_t qr[T::QI];
   load_q<D, M>(qr, Q + head, qrow, g, qvalid, scale_log2);
   const int bk = bk_sub * CK;
-  const int nb = block_list<NT>(dense, (N + bk - 1) / bk, n_k, row_ptr, col_idx, col_len, r, flag,
-                                list, wcount);
-  const int S = nb * bk_sub;
+  const bool all = !PV || dense;
+  const int S = all ? (N + CK - 1) / CK
+                    : bk_sub * block_list<NT>(n_k, row_ptr, col_idx, col_len, r, flag, list, wcount);
   auto key_of = [&](int x) -> int {
     const int y = x < S ? x : S - 1;
+    if (all) return y * CK;
     const int j = y / bk_sub;
     return __builtin_amdgcn_readfirstlane((int)list[j]) * bk + (y - j * bk_sub) * CK;
   };
