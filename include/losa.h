@@ -112,12 +112,12 @@ losa_status losa_calibrate_mass(const void* q, const void* k, losa_dtype dtype, 
  *
  * For each row r: order the row's key blocks by decreasing mass, ties by the
  * smaller block index (the paper leaves ties arbitrary); keep the shortest
- * prefix whose cumulative mass (summed in integer units of 2^-56, so exact to
- * n_k 2^-56) reaches tau (the exact fp32 value passed).  tau >= 1 keeps every
- * key block that holds a valid key, so the sparse forward then equals dense
- * attention.  A row whose masses never reach tau also keeps every such block.
- * Rows of query blocks with no valid query are empty.  Masses that are
- * negative or NaN count as 0.
+ * prefix whose cumulative mass (summed in integers, exact to n_k 2^-55 tau)
+ * reaches tau (the exact fp32 value passed).  tau >= 1 keeps every key block
+ * that holds a valid key, so the sparse forward then equals dense attention.  A
+ * row whose masses never reach tau also keeps every such block.  Rows of query
+ * blocks with no valid query are empty.  Masses that are negative or NaN count
+ * as 0; they need not sum to 1, and tau may be as small as they are.
  *
  * mass              fp32 [B][H][n_q][n_k] (e.g. from losa_calibrate_mass).
  * row_ptr           out, int32 [B*H*n_q + 1]: row_ptr[0] = 0, row_ptr[end] = nnz.

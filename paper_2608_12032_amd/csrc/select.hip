@@ -14,22 +14,27 @@
 //                2) by 1 with target min(topk, blocks holding a real key).
 //                tau >= 1 keeps every key block that holds a real key, and so
 //                does a row that never reaches tau.  The kept blocks go to a
-//                bit mask per row, their number to the row's count.
+//                bit mask per row, and the mask's bits counted to the row's
+//                count.
 //   scan_counts  one workgroup: exclusive scan of the counts -> row_ptr.
 //   compact_rows one wave per row: the flagged block ids, ascending, at
 //                col_idx[row_ptr[r] ...].
 //
-// Sums.  What decides is the sum of integer weights in units of 2^-56 (a mass
-// of 1 and more counts as 1, which reaches every tau): independent of the
-// order and within n_k 2^-56 of the exact sum.  A step of the search first
-// adds fp32 masses and turns to the integers only where that sum is within its
-// rounding error of tau.
+// Sums.  What decides is the sum of integer weights, masses in units of 2^-56
+// of the least power of two 2^-e above tau (a mass of 2^-e and more counts as
+// 2^-e, which reaches tau): independent of the order and within n_k 2^-55 tau of
+// the exact sum, whatever the size of tau.  A step of the search first adds fp32
+// masses and turns to the integers only where that sum is within 2^-19 tau of
+// tau.  Its rounding error is less than that by 2^-21 tau, far more than the
+// integers truncate: what the fp32 sum says is reached or not, the integers say
+// too, so the cut is always among the blocks in play.
 //
 // Bound: the search's compare, select and add per block and step, and reading
 // the masses.  At 22,296 rows of 3,716 masses (331 MB): select_rows 163 us
 // (2.0 TB/s), where a bitonic sort of each row's 4,096 keys in LDS took 2,314
 // us of barrier steps; compact_rows 33 us (110 us from byte flags), scan_counts
 // 7 us (29 us with one row per load).
+#include <cmath>
 #include <type_traits>
 
 #include "common.hpp"
@@ -46,15 +51,15 @@ __device__ __forceinline__ uint32_t mass_bits(float m) {  // negative and NaN ->
   return m > 0.f ? __float_as_uint(m) : 0u;
 }
 
-// A mass in units of 2^-56, truncated: hi in units of 2^-30 and lo < 2^26.
-__device__ __forceinline__ void split_mass(float m, uint32_t* hi, uint32_t* lo) {
-  const float x = m * 0x1p30f;
+// m 2^e in units of 2^-56, truncated: hi in units of 2^-30 and lo < 2^26.
+__device__ __forceinline__ void split_mass(float m, int e, uint32_t* hi, uint32_t* lo) {
+  const float x = __builtin_ldexpf(m, e + 30);
   *hi = (uint32_t)x;
   *lo = (uint32_t)(__builtin_amdgcn_fractf(x) * 0x1p26f);
 }
-__device__ __forceinline__ uint64_t mass_weight(uint32_t bits) {
+__device__ __forceinline__ uint64_t mass_weight(uint32_t bits, int e) {
   uint32_t hi, lo;
-  split_mass(fminf(__uint_as_float(bits), 1.f), &hi, &lo);
+  split_mass(fminf(__builtin_ldexpf(__uint_as_float(bits), e), 1.f), 0, &hi, &lo);
   return ((uint64_t)hi << 26) + lo;
 }
 
@@ -114,7 +119,7 @@ __host__ __device__ inline size_t mask_stride(int n_k) {
 template <int V, bool TOPK>
 __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 64 ? 1 : (TOPK ? 3 : 4))))
     select_rows_kernel(const float* __restrict__ mass, int rows, int n_q, int n_k, int n_kv, int N,
-                       int block_q, float tau, int topk, int32_t* __restrict__ counts,
+                       int block_q, float tau, int e, int topk, int32_t* __restrict__ counts,
                        uint8_t* __restrict__ masks) {
   __shared__ uint64_t keys[SEL_ROWS][64];
   const int lane = threadIdx.x & 63;
@@ -127,7 +132,6 @@ __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 
   uint32_t bits[V];
   uint32_t cut = 0;  // kept: bits > cut, or equal and j <= cut_j
   int cut_j = -1;
-  int kept_n = 0;
   if (!all) {
     // (past the row's end the resource reads zero: a branch per load would
     // wait out each one's latency)
@@ -137,11 +141,13 @@ __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 
       bits[u] = __builtin_amdgcn_raw_buffer_load_b32(mrs, 4 * lane, 256 * u, 0);
 #pragma unroll
     for (int u = 0; u < V; ++u) bits[u] = mass_bits(__uint_as_float(bits[u]));
-    uint64_t target = TOPK ? (uint64_t)min(topk, n_kv) : mass_weight(__float_as_uint(tau));
-    if (target == 0) target = 1;
+    const uint64_t target =
+        TOPK ? (uint64_t)min(topk, n_kv) : mass_weight(__float_as_uint(tau), e);
+    // (the lambdas are inlined in every place: called, they would take the row's
+    // registers through memory, 970 us instead of 195 at the size above)
     // weight of the blocks with bits >= c, c > 0 (threshold rule: if it is
-    // below 2; the high parts then add up to less than 2^32)
-    auto weight_from = [&](uint32_t c) -> uint64_t {
+    // below 2^57; the high parts then add up to less than 2^32)
+    auto weight_from = [&](uint32_t c) __attribute__((always_inline)) -> uint64_t {
       uint32_t hi = 0, lo = 0;
 #pragma unroll
       for (int u = 0; u < V; ++u) {
@@ -150,7 +156,7 @@ __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 
         } else {
           uint32_t h, l;
           const uint32_t b = fresh(bits[u]);
-          split_mass(b >= c ? __uint_as_float(b) : 0.f, &h, &l);
+          split_mass(b >= c ? __uint_as_float(b) : 0.f, e, &h, &l);
           hi += h;
           lo += l;
         }
@@ -159,7 +165,7 @@ __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 
       return ((uint64_t)wave_total(hi) << 26) + ((uint64_t)wave_total(lo >> 16) << 16) +
              wave_total(lo & 0xffffu);
     };
-    auto reached = [&](uint32_t c) -> bool {
+    auto reached = [&](uint32_t c) __attribute__((always_inline)) -> bool {
       if constexpr (!TOPK) {
         float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -193,7 +199,7 @@ __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 
     int shift = 31;      // T's bits from here up are settled
     // whether block u of this lane shares them (threshold rule: a block of
     // mass 0 cannot move the cut; top-k: it can, if there is such a block)
-    auto shares = [&](int u) -> bool {
+    auto shares = [&](int u) __attribute__((always_inline)) -> bool {
       const uint32_t lo = TOPK ? T : max(T, 1u);
       return fresh(bits[u]) - lo < T + (1u << shift) - lo && (!TOPK || lane < n_k - 64 * u);
     };
@@ -218,11 +224,8 @@ __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 
 
     if (!all) {
       const uint64_t base = weight_from(T + (1u << shift));  // heavier than those in play
-      int above = 0;
-#pragma unroll
-      for (int u = 0; u < V; ++u) above += __popcll(__ballot(fresh(bits[u]) >= T + (1u << shift)));
       if (in_play <= 64) {
-        // one block in play per lane; its rank and the weight before it
+        // one block in play per lane, and the weight before it
         int at = 0;
         uint32_t id = lane;
 #pragma unroll
@@ -237,26 +240,20 @@ __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         const uint64_t key = keys[w][lane < in_play ? lane : 0];
-        const uint64_t own = TOPK ? 1 : mass_weight(~(uint32_t)(key >> 32));
+        const uint64_t own = TOPK ? 1 : mass_weight(~(uint32_t)(key >> 32), e);
         uint64_t before = base;
-        int rank = 0;
-        for (int y = 0; y < in_play; ++y) {
-          const bool heavier = read_lane(key, y) < key;
-          before += heavier ? read_lane(own, y) : 0;
-          rank += heavier;
-        }
+        for (int y = 0; y < in_play; ++y)
+          before += read_lane(key, y) < key ? read_lane(own, y) : 0;
         const int at_cut = __builtin_ctzll(
             __ballot(lane < in_play && before < target && before + own >= target));
         const uint64_t cut_key = read_lane(key, at_cut);
         cut = ~(uint32_t)(cut_key >> 32);
         cut_j = (int)(uint32_t)cut_key;
-        kept_n = above + __builtin_amdgcn_readlane(rank, at_cut) + 1;
       } else {
         // more than 64 blocks of mass T: the first of them by index
-        const uint64_t each = TOPK ? 1 : mass_weight(T);
+        const uint64_t each = TOPK ? 1 : mass_weight(T, e);
         int need = (int)((target - base + each - 1) / each);
         cut = T;
-        kept_n = above + need;
 #pragma unroll
         for (int u = 0; u < V; ++u) {
           const uint64_t bal = __ballot(shares(u));
@@ -271,6 +268,7 @@ __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 
   }
 
   uint64_t word = 0;  // lane u: word u of the row's mask
+  int count = 0;      // its bits, so that the compaction writes as many ids as it has room for
 #pragma unroll
   for (int u = 0; u < V; ++u) {
     const uint32_t b = all ? 0 : fresh(bits[u]);
@@ -279,6 +277,7 @@ __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 
                                 (b > cut || (b == cut && lane <= cut_j - 64 * u));
     const uint64_t bal = __ballot(kept);
     if (lane == u) word = bal;
+    count += __popcll(bal);
   }
   uint8_t* mask = masks + (size_t)r * mask_stride(n_k);
   if (lane < (n_k + 63) / 64) {
@@ -287,7 +286,7 @@ __global__ void __launch_bounds__(SEL_T) __attribute__((amdgpu_waves_per_eu(V < 
     else
       reinterpret_cast<uint64_t*>(mask)[lane] = word;
   }
-  if (lane == 0) counts[r] = all ? (empty ? 0 : n_kv) : kept_n;
+  if (lane == 0) counts[r] = count;
 }
 
 constexpr int SCAN_T = 1024;
@@ -365,12 +364,14 @@ template <int V>
 void launch_sel(const float* mass, int rows, int n_q, int n_k, int n_kv, int N, int block_q,
                 float tau, int topk, int32_t* counts, uint8_t* masks, hipStream_t stream) {
   const dim3 grid((rows + SEL_ROWS - 1) / SEL_ROWS);
+  int tau_exp = 0;  // tau in [2^(tau_exp - 1), 2^tau_exp)
+  frexpf(tau, &tau_exp);
   if (topk > 0)
     hipLaunchKernelGGL((select_rows_kernel<V, true>), grid, dim3(SEL_T), 0, stream, mass, rows,
-                       n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks);
+                       n_q, n_k, n_kv, N, block_q, tau, -tau_exp, topk, counts, masks);
   else
     hipLaunchKernelGGL((select_rows_kernel<V, false>), grid, dim3(SEL_T), 0, stream, mass, rows,
-                       n_q, n_k, n_kv, N, block_q, tau, topk, counts, masks);
+                       n_q, n_k, n_kv, N, block_q, tau, -tau_exp, topk, counts, masks);
 }
 
 }  // namespace

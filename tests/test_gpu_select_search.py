@@ -3,7 +3,10 @@ index), masses that differ only in their lowest bits (every stage of the
 search), more and fewer than 64 blocks with the cut's bits, masses over 1, infinite,
 negative and NaN ones, rows that never reach tau, and each width of a row's bit
 mask, both rules, against the oracle.  The masses are exact sums in fp64 and in
-units of 2^-56, so the sets must be equal, with no exemption."""
+units of 2^-56 of the threshold's power of two, so the sets must be equal, with
+no exemption.  Then masses and thresholds scaled down together."""
+from fractions import Fraction
+
 import numpy as np
 import pytest
 import torch
@@ -72,3 +75,47 @@ def test_selection_search(L, kind):
             want_rp, want_ci, _ = O.select_blocks_topk(m64, N, Cq, Ck, k)
             assert np.array_equal(got, want_rp), (n_k, k)
             assert np.array_equal(ci[:got[-1]].cpu().numpy(), want_ci), (n_k, k)
+
+
+@pytest.mark.parametrize("kind", [k for k in KINDS if k != "large"])
+@pytest.mark.parametrize("down", [20, 47, 100])
+def test_small_masses_and_threshold(L, kind, down):
+    """Masses that do not sum to one, and a threshold as small as they are: the
+    rule only compares sums, so masses and threshold scaled by a power of two
+    keep the same sets."""
+    rng = np.random.default_rng(60 + KINDS.index(kind))
+    for n_k in (7, 64, 257, 1025, 4096):
+        Cq, Ck = (128, 32) if n_k % 4 == 0 else (64, 64)
+        N = n_k * Ck - 5
+        n_q = n_k * Ck // Cq
+        print(f"[gpu-select-search] small {kind} 2^-{down} n_k={n_k} rows={n_q}", flush=True)
+        m = np.ldexp(masses(kind, n_q, n_k, rng), -down).astype(np.float32)
+        mt = torch.from_numpy(m.reshape(1, 1, n_q, n_k)).cuda()
+        m64 = np.where(m > 0, m, 0).astype(np.float64).reshape(1, 1, n_q, n_k)
+        for tau in (0.5, 0.75, 1.0 - 2.0 ** -10):
+            t = float(np.ldexp(np.float32(tau), -down))
+            rp, ci = L.losa_select_blocks(mt, N, Cq, Ck, t)
+            got = rp.cpu().numpy()
+            want_rp, want_ci, _ = O.select_blocks(m64, N, Cq, Ck, t)
+            assert np.array_equal(got, want_rp), (n_k, tau)
+            assert np.array_equal(ci[:got[-1]].cpu().numpy(), want_ci), (n_k, tau)
+
+
+# (blocks, mass of each, tau): the first ceil(tau / mass) of them, by whole-number
+# arithmetic on the fp32 values; the last one is below the normal range
+EQUAL = [(1000, 1e-18, 5e-16), (4096, 1e-17, 1e-14), (1000, 1e-16, 5e-14), (48, 1e-18, 1.5e-17),
+         (4096, 1e-12, 1e-9), (1024, 1e-10, 1e-7), (3, 1e-38, 1.5e-38), (1000, 2e-45, 1e-42)]
+
+
+@pytest.mark.parametrize("n_k,m,tau", EQUAL)
+def test_equal_tiny_masses(L, n_k, m, tau):
+    m, tau = Fraction(float(np.float32(m))), Fraction(float(np.float32(tau)))
+    want = -(-tau // m)
+    assert 0 < want < n_k
+    Cq, Ck = (128, 32) if n_k % 4 == 0 else (64, 64)
+    rows = n_k * Ck // Cq
+    mt = torch.full((1, 1, rows, n_k), float(m), dtype=torch.float32, device="cuda")
+    rp, ci = L.losa_select_blocks(mt, n_k * Ck, Cq, Ck, float(tau))
+    torch.cuda.synchronize()
+    assert torch.equal(rp.cpu(), (torch.arange(rows + 1) * want).int())
+    assert torch.equal(ci[:rows * want].cpu(), torch.arange(want, dtype=torch.int32).repeat(rows))
