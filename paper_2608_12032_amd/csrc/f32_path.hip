@@ -2,29 +2,37 @@
 // (Sec. 4.2, Eq. (4)) on the fp32 matrix instructions (fp32 products, fp32
 // accumulation; no input is rounded).
 //
-// Tiles.  A wave owns M query rows (32, or 16 for small calls) and walks
-// 32-key sub-tiles.  It computes S^T = K Q^T, so that a lane holds scores of
-// ONE query (column = lane % M) and the online softmax is in-lane plus an
-// exchange between the lane groups (lane / M), and O^T = V^T P^T, whose B
-// operand of k-step t is register t of the score tile as it stands:
+// Tiles.  A wave owns groups of M query rows (attention and normalisers: one or
+// two groups of 16; masses: one of 32) and walks 32-key sub-tiles.  It computes
+// S^T = K Q^T, so that a lane holds scores of ONE query of each group (column =
+// lane % M) and the online softmax is in-lane plus an exchange between the lane
+// groups (lane / M), and O^T = V^T P^T, whose B operand of k-step t is register t
+// of the score tile as it stands:
 //   score register t of lane group g  <->  key (t/4) * 4G + 4g + t%4,  G = 64/M.
 // The contraction order over d is free, so lane group g takes
 // d = 4 (G i + g) .. + 3 and one 16-byte load of a K row feeds four matrix
-// instructions; row m of O^T block b stands for d = VC (M (b / VC) + m) + b % VC,
-// VC = 4 (2 at d = 64, M = 32), so a load of VC floats feeds VC d blocks.  K and V go from global
-// memory straight to registers: a 32-key sub-tile is 32 KiB for 8,192
-// matrix cycles (M = 32, d = 128), 16 bytes per clock and CU (32 at M = 16),
-// so staging in LDS would save nothing.  A sub-tile's loads form one stream, K
-// then V, and run kLead loads ahead of the products that use them, across
-// sub-tiles.//
-// Split.  The waves of a workgroup share the M rows and take the row's
+// instructions per row group; row m of O^T block b stands for
+// d = 4 (16 (b / 4) + m) + b % 4, so a 16-byte load of V feeds four d blocks.
+// K and V go from global memory straight to registers: a 32-key sub-tile is 32
+// KiB for 8,192 matrix cycles (two groups, d = 128), 16 bytes per clock and CU
+// (32 with one group), so staging in LDS would save nothing.  A sub-tile's loads
+// form one stream, K then V, and run kLead loads ahead of the products that use
+// them, across sub-tiles.  A row's arithmetic is the same in either group and with
+// either number of them, so the number may follow from the size of the call
+// without any effect on a row's bits.
+//
+// Split.  The waves of a workgroup share its rows and take the row's
 // sub-tiles in turn; their softmax states (max, sum, O) are merged in a fixed
 // order through LDS at the end; two waves per SIMD cover each other's softmax.
 //
 // Bound: the fp32 matrix rate (157 TFLOP/s).  Attention over full rows, d =
-// 128: 126 TFLOP/s at N = 8,192 x 4 heads, 121 at 4,096, 104 at 4,480 (the last
-// round a fifth full), 33 at 512 x 4 (128 tiles of one round).  A thread per query row with plain fma and its keys in LDS, which
-// this replaced, ran 7.7 TFLOP/s at N = 4,437 x 4 (5.2 ms, now 0.41).
+// 128: 123 TFLOP/s at N = 8,192 x 3 heads, 118 at 4,096 x 4, 100 at 4,437 x 4
+// (the last round a fifth full), 33 at 512 x 4 (128 tiles of one round).  A thread
+// per query row with plain fma and its keys in LDS, which this replaced, ran 7.7
+// TFLOP/s at N = 4,437 x 4 (5.2 ms, now 0.40).  Two groups of 16 rows on 16x16x4
+// instructions against one of 32 on 32x32x2, whose rows round differently from
+// those of a 16-row tile: 2 % slower at d = 128 (1,090 / 1,072 us at 12 x 4,437),
+// 4 % faster at d = 64 (590 / 614).
 // The construction step's masses take one sweep over the keys (175 us at N =
 // 4,437 x 4 heads and 11 us for their reduction; two sweeps: 238 + 175).
 //
@@ -48,8 +56,8 @@ namespace {
 constexpr int CK = 32;    // keys per sub-tile
 constexpr int kLead = 8;  // loads in flight ahead of their use, per wave
 
-// Shapes of a wave's tile of M query rows.  A sub-tile's operands arrive as a
-// stream of KC chunks of K (16 bytes a lane), then VN of V (VC floats a lane).
+// Shapes of a wave's groups of M query rows.  A sub-tile's operands arrive as a
+// stream of KC chunks of K, then (M = 16) VN of V, 16 bytes a lane.
 template <int D, int M>
 struct F32Tile {
   static constexpr int G = 64 / M;             // lane groups
@@ -57,11 +65,9 @@ struct F32Tile {
   static constexpr int KT = CK / M;            // M-key tiles per sub-tile
   static constexpr int QI = D / (4 * G);       // 16-byte chunks of a row per lane
   static constexpr int DB = D / M;             // d blocks of O^T
-  static constexpr int VC = DB >= 4 ? 4 : DB;  // floats per V load
-  static constexpr int VP = DB / VC;           // V loads per score register
+  static constexpr int VP = DB / 4;            // V loads per score register
   static constexpr int KC = KT * QI;
   static constexpr int VN = KT * SR * VP;
-  static_assert(DB % VC == 0, "a lane's part of a V row is whole loads");
   static_assert(KC % kLead == 0 && VN % kLead == 0, "the stream fills the ring evenly");
 };
 
@@ -101,15 +107,9 @@ __device__ __forceinline__ f32x4_t load_k(const float* K, int key0, int c, int l
 template <int D, int M>
 __device__ __forceinline__ f32x4_t load_v(const float* V, int key0, int c, int lm, int g) {
   using T = F32Tile<D, M>;
-  typedef float vec_t __attribute__((ext_vector_type(T::VC)));
   const int t = c / T::VP % T::SR, kt = c / T::VP / T::SR;
-  const vec_t y = *reinterpret_cast<const vec_t*>(
-      V + (size_t)(key0 + 4 * g) * D + lm * T::VC + (kt * M + score_key<M>(t, 0)) * D +
-      c % T::VP * T::VC * M);
-  f32x4_t x = f32x4_t{};
-#pragma unroll
-  for (int e = 0; e < T::VC; ++e) x[e] = y[e];
-  return x;
+  return *reinterpret_cast<const f32x4_t*>(V + (size_t)(key0 + 4 * g) * D + lm * 4 +
+                                           (kt * M + score_key<M>(t, 0)) * D + c % T::VP * 4 * M);
 }
 
 // The query operand, scaled; padding rows (!valid) read as 0, so that their
@@ -128,46 +128,54 @@ __device__ __forceinline__ void load_q(f32x4_t* qr, const float* Q, int row, int
 }
 
 // Scores of a sub-tile in log2 units: chunk c of K, in ring[c % kLead], against
-// the query operand (two accumulation chains, so that no product waits for the
-// one before it).  issue(c) refills the slot just used.  Keys at or beyond
-// kvalid get -inf.
-template <int D, int M, typename Issue>
+// the query operands of RG row groups (group r's at qr[r * QI], its scores at
+// s[r * KT]; two accumulation chains each, so that no product waits for the one
+// before it).  issue(c) refills the slot just used.  Keys at or beyond kvalid get
+// -inf.
+template <int D, int M, int RG, typename Issue>
 __device__ __forceinline__ void scores(f32x4_t* ring, const f32x4_t* qr, int g, int kvalid,
                                        typename F32Acc<M>::type* s, Issue&& issue) {
   using T = F32Tile<D, M>;
   using A = F32Acc<M>;
-  typename A::type odd[T::KT];
+  typename A::type odd[RG * T::KT];
 #pragma unroll
-  for (int kt = 0; kt < T::KT; ++kt) {
-    s[kt] = typename A::type{};
-    odd[kt] = typename A::type{};
+  for (int x = 0; x < RG * T::KT; ++x) {
+    s[x] = typename A::type{};
+    odd[x] = typename A::type{};
   }
 #pragma unroll
   for (int c = 0; c < T::KC; ++c) {
     const int kt = c % T::KT, i = c / T::KT;
     const f32x4_t a = ring[c % kLead];
-    s[kt] = A::mfma(a[0], qr[i][0], s[kt]);
-    odd[kt] = A::mfma(a[1], qr[i][1], odd[kt]);
-    s[kt] = A::mfma(a[2], qr[i][2], s[kt]);
-    odd[kt] = A::mfma(a[3], qr[i][3], odd[kt]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int r = 0; r < RG; ++r) {
+        typename A::type& x = (e & 1) == 0 ? s[r * T::KT + kt] : odd[r * T::KT + kt];
+        x = A::mfma(a[e], qr[r * T::QI + i][e], x);
+      }
     issue(c);
     __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
-  for (int kt = 0; kt < T::KT; ++kt) s[kt] += odd[kt];
+  for (int x = 0; x < RG * T::KT; ++x) s[x] += odd[x];
   if (kvalid < CK) {
 #pragma unroll
-    for (int kt = 0; kt < T::KT; ++kt)
+    for (int x = 0; x < RG * T::KT; ++x)
 #pragma unroll
       for (int t = 0; t < T::SR; ++t)
-        if (kt * M + score_key<M>(t, g) >= kvalid) s[kt][t] = -INFINITY;
+        if (x % T::KT * M + score_key<M>(t, g) >= kvalid) s[x][t] = -INFINITY;
   }
 }
 
 template <int M>
 __device__ __forceinline__ float group_max(float x) {
-  x = fmaxf(x, __shfl_xor(x, 32));
-  if constexpr (M == 16) x = fmaxf(x, __shfl_xor(x, 16));
+  x = max_with_partner(x);
+  if constexpr (M == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false,
+                                                    false);
+    x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
   return x;
 }
 template <int M>
@@ -245,18 +253,20 @@ __device__ int block_list(int n_k, const int32_t* __restrict__ row_ptr,
 
 constexpr int kF32Waves = 8;  // waves of a workgroup (key splits): two per SIMD
 
-// Attention of M query rows over their query block's key blocks (bk_sub
+// Attention of 16 RG query rows over their query block's key blocks (bk_sub
 // 32-key sub-tiles each).  PV: O and, if given, lse (natural log).  !PV: only
-// the normaliser, in log2 units, to lse (dense).  Dense: every sub-tile that
-// holds a valid key, in order and from no list, so that no number of key blocks
-// is too large (the calibration takes any).
-template <int D, int M, bool PV>
+// the normaliser, in log2 units, to lse.  DENSE: every sub-tile that holds a valid
+// key, in order and from no list, so that no number of key blocks is too large
+// (the calibration takes any).
+template <int D, int RG, bool PV, bool DENSE>
 __global__ void __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_per_eu(2)))
     attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
                     const float* __restrict__ V, const int32_t* __restrict__ row_ptr,
                     const int32_t* __restrict__ col_idx, int64_t col_len, float* __restrict__ O,
                     float* __restrict__ lse, int tile0, int blk, int bk_sub, int n_k, int N,
-                    int n_pad, float scale_log2, int dense) {
+                    int n_pad, float scale_log2) {
+  constexpr int M = 16;
+  constexpr int ROWS = M * RG;
   using T = F32Tile<D, M>;
   using A = F32Acc<M>;
   constexpr int NWV = kF32Waves;
@@ -265,41 +275,50 @@ __global__ void __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_pe
   __shared__ uint8_t flag[kSparseFwdMaxNk];
   __shared__ uint16_t list[kSparseFwdMaxNk];
   __shared__ int wcount[NWV];
-  __shared__ float mpart[NWV * M];
-  __shared__ double lpart[NWV * M];
-  __shared__ __attribute__((aligned(16))) float opart[PV ? NWV * M * LD : 4];
+  __shared__ float mpart[NWV * ROWS];
+  __shared__ double lpart[NWV * ROWS];
+  __shared__ __attribute__((aligned(16))) float opart[PV ? NWV * ROWS * LD : 4];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lm = lane % M, g = lane / M;
-  const int tiles = n_pad / M;  // per head
+  const int tiles = n_pad / ROWS;  // per head
   const int x0 = tile0 + xcd_remap(blockIdx.x, gridDim.x);
   const int bh = x0 / tiles;
-  const int row0 = (x0 - bh * tiles) * M;
+  const int row0 = (x0 - bh * tiles) * ROWS;
   const int r = bh * (n_pad / blk) + row0 / blk;
   const size_t head = (size_t)bh * n_pad * D;
-  const int qrow = row0 + lm;
-  const bool qvalid = qrow < N;
 
-  f32x4_t qr[T::QI];
-  load_q<D, M>(qr, Q + head, qrow, g, qvalid, scale_log2);
+  f32x4_t qr[RG * T::QI];
+#pragma unroll
+  for (int rg = 0; rg < RG; ++rg) {
+    const int qrow = row0 + rg * M + lm;
+    load_q<D, M>(qr + rg * T::QI, Q + head, qrow, g, qrow < N, scale_log2);
+  }
   const int bk = bk_sub * CK;
-  const bool all = !PV || dense;
-  const int S = all ? (N + CK - 1) / CK
-                    : bk_sub * block_list<NT>(n_k, row_ptr, col_idx, col_len, r, flag, list, wcount);
+  int S;
+  if constexpr (DENSE)
+    S = (N + CK - 1) / CK;
+  else
+    S = block_list<NT>(n_k, row_ptr, col_idx, col_len, r, flag, list, wcount) * bk_sub;
   auto key_of = [&](int x) -> int {
     const int y = x < S ? x : S - 1;
-    if (all) return y * CK;
+    if constexpr (DENSE) return y * CK;
     const int j = y / bk_sub;
     return __builtin_amdgcn_readfirstlane((int)list[j]) * bk + (y - j * bk_sub) * CK;
   };
 
-  float m = kNegBig;
-  double l = 0.0;
-  typename A::type o[T::DB];
-  if constexpr (PV) {
+  float m[RG];
+  double l[RG];
+  typename A::type o[RG][T::DB];
 #pragma unroll
-    for (int b = 0; b < T::DB; ++b) o[b] = typename A::type{};
+  for (int rg = 0; rg < RG; ++rg) {
+    m[rg] = kNegBig;
+    l[rg] = 0.0;
+    if constexpr (PV) {
+#pragma unroll
+      for (int b = 0; b < T::DB; ++b) o[rg][b] = typename A::type{};
+    }
   }
   constexpr int NC = T::KC + (PV ? T::VN : 0);  // chunks of a sub-tile
   const float* Kh = K + head;
@@ -323,28 +342,40 @@ __global__ void __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_pe
       else
         ring[c % kLead] = load_k<D, M>(Kh, next, n - NC, lm, g);
     };
-    typename A::type s[T::KT];
-    scores<D, M>(ring, qr, g, N - key0, s, issue);
-    const float mx = tile_max<D, M>(s);
-    if (__ballot(mx > m) != 0) {
-      const float m_new = fmaxf(m, mx);
-      const float alpha = fast_exp2(m - m_new);
-      m = m_new;
-      l *= (double)alpha;
-      if constexpr (PV) {
+    typename A::type s[RG * T::KT];
+    scores<D, M, RG>(ring, qr, g, N - key0, s, issue);
+    float mx[RG];
+    bool raise = false;
 #pragma unroll
-        for (int b = 0; b < T::DB; ++b) o[b] *= alpha;
+    for (int rg = 0; rg < RG; ++rg) {
+      mx[rg] = tile_max<D, M>(s + rg * T::KT);
+      raise = raise || mx[rg] > m[rg];
+    }
+    if (__ballot(raise) != 0) {
+#pragma unroll
+      for (int rg = 0; rg < RG; ++rg) {
+        const float m_new = fmaxf(m[rg], mx[rg]);
+        const float alpha = fast_exp2(m[rg] - m_new);  // 1 where the max stays
+        m[rg] = m_new;
+        l[rg] *= (double)alpha;
+        if constexpr (PV) {
+#pragma unroll
+          for (int b = 0; b < T::DB; ++b) o[rg][b] *= alpha;
+        }
       }
     }
-    l += (double)tile_exp<D, M>(s, m);
+#pragma unroll
+    for (int rg = 0; rg < RG; ++rg) l[rg] += (double)tile_exp<D, M>(s + rg * T::KT, m[rg]);
     if constexpr (PV) {
 #pragma unroll
       for (int c = 0; c < T::VN; ++c) {
         const int p = c % T::VP, t = c / T::VP % T::SR, kt = c / T::VP / T::SR;
         const f32x4_t a = ring[(T::KC + c) % kLead];
 #pragma unroll
-        for (int e = 0; e < T::VC; ++e)
-          o[p * T::VC + e] = A::mfma(a[e], s[kt][t], o[p * T::VC + e]);
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int rg = 0; rg < RG; ++rg)
+            o[rg][p * 4 + e] = A::mfma(a[e], s[rg * T::KT + kt][t], o[rg][p * 4 + e]);
         issue(T::KC + c);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -354,50 +385,53 @@ __global__ void __launch_bounds__(64 * kF32Waves) __attribute__((amdgpu_waves_pe
 
   // merge the waves' states: the common max, then sums and outputs rescaled to
   // it, added in wave order
-  const double lw = group_sum<M>(l);
-  if (g == 0) {
-    mpart[w * M + lm] = m;
-    lpart[w * M + lm] = lw;
-  }
-  if constexpr (PV) {
-    // register t of d block b holds d = VC * (M (b / VC) + row) + b % VC
 #pragma unroll
-    for (int t = 0; t < T::SR; ++t)
+  for (int rg = 0; rg < RG; ++rg) {
+    const int at = w * ROWS + rg * M + lm;
+    const double lw = group_sum<M>(l[rg]);
+    if (g == 0) {
+      mpart[at] = m[rg];
+      lpart[at] = lw;
+    }
+    if constexpr (PV) {
+      // register t of d block b holds d = 4 (16 (b / 4) + row) + b % 4
 #pragma unroll
-      for (int b = 0; b < T::DB; ++b)
-        opart[(w * M + lm) * LD + T::VC * (b / T::VC * M + score_key<M>(t, g)) + b % T::VC] =
-            o[b][t];
+      for (int t = 0; t < T::SR; ++t)
+#pragma unroll
+        for (int b = 0; b < T::DB; ++b)
+          opart[at * LD + 4 * (b / 4 * M + score_key<M>(t, g)) + b % 4] = o[rg][b][t];
+    }
   }
   __syncthreads();
   auto merged = [&](int row, float* wgt) -> double {  // sum of row `row`, weight of each wave
     float mm = kNegBig;
 #pragma unroll
-    for (int y = 0; y < NWV; ++y) mm = fmaxf(mm, mpart[y * M + row]);
+    for (int y = 0; y < NWV; ++y) mm = fmaxf(mm, mpart[y * ROWS + row]);
     double lt = 0.0;
 #pragma unroll
     for (int y = 0; y < NWV; ++y) {
-      wgt[y] = fast_exp2(mpart[y * M + row] - mm);
-      lt += lpart[y * M + row] * (double)wgt[y];
+      wgt[y] = fast_exp2(mpart[y * ROWS + row] - mm);
+      lt += lpart[y * ROWS + row] * (double)wgt[y];
     }
     wgt[NWV] = mm;
     return lt;
   };
   float wgt[NWV + 1];
-  if (tid < M && lse != nullptr) {
+  if (tid < ROWS && lse != nullptr) {
     const float lf = (float)merged(tid, wgt);
     const float l2 = wgt[NWV] + __log2f(lf);
     const bool ok = row0 + tid < N && lf > 0.f;
     lse[(size_t)bh * n_pad + row0 + tid] = PV ? (ok ? l2 * kLn2 : -INFINITY) : l2;
   }
   if constexpr (PV) {
-    for (int idx = tid; idx < M * D / 4; idx += NT) {
+    for (int idx = tid; idx < ROWS * D / 4; idx += NT) {
       const int row = idx / (D / 4), d4 = (idx % (D / 4)) * 4;
       const float lf = (float)merged(row, wgt);
       const float inv = (row0 + row < N && lf > 0.f) ? 1.0f / lf : 0.f;
       f32x4_t acc = f32x4_t{};
 #pragma unroll
       for (int y = 0; y < NWV; ++y) {
-        const f32x4_t p = *reinterpret_cast<const f32x4_t*>(opart + (y * M + row) * LD + d4);
+        const f32x4_t p = *reinterpret_cast<const f32x4_t*>(opart + (y * ROWS + row) * LD + d4);
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[e] = fmaf(p[e], wgt[y], acc[e]);
       }
@@ -458,7 +492,7 @@ __global__ void __launch_bounds__(256)
     for (int c = 0; c < kLead; ++c) ring[c] = load_k<D, M>(Kh, key0, c, lm, g);
   };
   auto sub_scores = [&](int key0, int next) {
-    scores<D, M>(ring, qr, g, N - key0, s, [&](int c) {
+    scores<D, M, 1>(ring, qr, g, N - key0, s, [&](int c) {
       const int n = c + kLead;
       ring[c % kLead] = load_k<D, M>(Kh, n < T::KC ? key0 : next, n % T::KC, lm, g);
     });
@@ -572,7 +606,7 @@ __global__ void __launch_bounds__(256)
       const int key0 = j * bk + u * CK;
       const int next = u + 1 < subs ? key0 + CK : (j + KSP < j1 ? (j + KSP) * bk : key0);
       typename A::type s[T::KT];
-      scores<D, M>(ring, qr, g, N - key0, s, [&](int c) {
+      scores<D, M, 1>(ring, qr, g, N - key0, s, [&](int c) {
         const int n = c + kLead;
         ring[c % kLead] = load_k<D, M>(Kh, n < T::KC ? key0 : next, n % T::KC, lm, g);
       });
@@ -647,17 +681,20 @@ __global__ void __launch_bounds__(256)
   if (x < total) lse[x] = x % n_pad < N ? lse[x] * kLn2 : -INFINITY;
 }
 
-// Tile heights of a call with `tiles` 32-row tiles: how many of them run as
-// such, the rest as twice as many 16-row tiles.  A workgroup fills a CU and a
-// row's keys are not split over workgroups, so the time goes in rounds of 256
-// tiles; a round of 16-row tiles has half the work but the same K/V traffic.
-// Measured, one round of 32-row against one of 16-row tiles: 79 / 44 us at d =
-// 128 and 48 / 25 us at d = 64 (N = 2,048, 4 heads).  So at d = 128 whole
-// rounds are 32 rows high, and what is left over, if it is 128 tiles or fewer,
-// one round of 16 rows (560 tiles: 397 us, all 32 rows 455, all 16 rows 428).
-// At d = 64 such a call takes 16 rows throughout (560 tiles: 218 us, mixed 228,
-// all 32 rows 260).  Scores only (79 / 64 us, N = 4,437, d = 128) take one
-// height for all.
+// Tile heights of a call with `tiles` 32-row tiles: how many of them run as such
+// (two row groups a wave), the rest as twice as many 16-row tiles (one).  A
+// row's keys are not split over workgroups, and 256 tiles fill the matrix cores
+// of the CUs (where two 16-row tiles share one, at d = 64, each runs half as
+// fast), so the time goes in rounds of 256 tiles; a round of 16-row tiles has half
+// the work but the same K/V traffic.  Full rows of 32 64-key blocks, one round of
+// 32-row against one of 16-row tiles: 78 / 45 us at d = 128, 43 / 25 us at d = 64.
+// So at d = 128 whole rounds are 32 rows high, and what is left over, if it is 128
+// tiles or fewer, one round of 16 rows (8 rounds and 64 tiles: 663 us, all 32 rows
+// 688, all 16 rows 759).  At d = 64 such a call takes 16 rows throughout: the
+// second launch costs more than the better rounds give, up to 16 rounds (2 rounds
+// and 64 tiles: 108 us, mixed 111, all 32 rows 125; 16 and 64: 711, 721, 732).
+// Scores only take one height for all (N = 4,437, 4 heads, d = 128: 421 us a
+// calibration with 32 rows, 497 with 16; N = 4,096, one head: 118 / 103).
 template <bool PV>
 int64_t wide_tiles(int d, int64_t tiles) {
   const int64_t rest = tiles % 256;
@@ -666,21 +703,21 @@ int64_t wide_tiles(int d, int64_t tiles) {
   return 5 * r32 <= 4 * r16 ? tiles : 0;
 }
 
-template <int D, int M, bool PV>
+template <int D, int RG, bool PV, bool DENSE>
 hipError_t launch_attn(const void* q, const void* k, const void* v, int tile0, int64_t tiles,
                        int blk, int blk_k, int N, int n_pad, float scale, const int32_t* row_ptr,
                        const int32_t* col_idx, int64_t col_len, void* o, float* lse,
                        hipStream_t stream) {
   if (tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL((attn_f32_kernel<D, M, PV>), dim3((uint32_t)tiles), dim3(64 * kF32Waves), 0,
+  hipLaunchKernelGGL((attn_f32_kernel<D, RG, PV, DENSE>), dim3((uint32_t)tiles), dim3(64 * kF32Waves), 0,
                      stream, static_cast<const float*>(q), static_cast<const float*>(k),
                      static_cast<const float*>(v), row_ptr, col_idx, col_len,
                      static_cast<float*>(o), lse, tile0, blk, blk_k / CK, n_pad / blk_k, N, n_pad,
-                     scale * kLog2e, row_ptr == nullptr);
+                     scale * kLog2e);
   return hipGetLastError();
 }
 
-template <bool PV>
+template <bool PV, bool DENSE>
 hipError_t launch_attn_any(int d, int blk, int blk_k, const void* q, const void* k, const void* v,
                            int BH, int N, int n_pad, float scale, const int32_t* row_ptr,
                            const int32_t* col_idx, int64_t col_len, void* o, float* lse,
@@ -688,13 +725,13 @@ hipError_t launch_attn_any(int d, int blk, int blk_k, const void* q, const void*
   const int64_t tiles = (int64_t)BH * (n_pad / 32), wide = wide_tiles<PV>(d, tiles);
   const int rest0 = (int)(2 * wide);  // first 16-row tile
   hipError_t err = hipErrorInvalidValue;
-#define LOSA_F32_ATTN(DD)                                                                        \
-  if (d == DD) {                                                                                 \
-    err = launch_attn<DD, 32, PV>(q, k, v, 0, wide, blk, blk_k, N, n_pad, scale, row_ptr,        \
-                                  col_idx, col_len, o, lse, stream);                             \
-    if (err == hipSuccess)                                                                       \
-      err = launch_attn<DD, 16, PV>(q, k, v, rest0, 2 * (tiles - wide), blk, blk_k, N, n_pad,    \
-                                    scale, row_ptr, col_idx, col_len, o, lse, stream);           \
+#define LOSA_F32_ATTN(DD)                                                                         \
+  if (d == DD) {                                                                                  \
+    err = launch_attn<DD, 2, PV, DENSE>(q, k, v, 0, wide, blk, blk_k, N, n_pad, scale, row_ptr,   \
+                                        col_idx, col_len, o, lse, stream);                        \
+    if (err == hipSuccess)                                                                        \
+      err = launch_attn<DD, 1, PV, DENSE>(q, k, v, rest0, 2 * (tiles - wide), blk, blk_k, N,      \
+                                          n_pad, scale, row_ptr, col_idx, col_len, o, lse, stream); \
   }
   LOSA_F32_ATTN(64)
   LOSA_F32_ATTN(128)
@@ -755,7 +792,7 @@ hipError_t masses(int d, int blk, int blk_k, const void* q, const void* k, int B
                   int n_pad, float scale, float* mass, float* scratch, hipStream_t stream) {
   if (scratch != nullptr) {
     const hipError_t err =
-        launch_attn_any<false>(d, blk, blk_k, q, k, nullptr, BH, N, n_pad, scale, nullptr, nullptr,
+        launch_attn_any<false, true>(d, blk, blk_k, q, k, nullptr, BH, N, n_pad, scale, nullptr, nullptr,
                                0, nullptr, scratch, stream);
     if (err != hipSuccess) return err;
   }
@@ -776,8 +813,8 @@ hipError_t launch_sparse_fwd_f32(int d, int blk, int blk_k, const void* q, const
                                  const void* v, int B, int H, int N, int n_pad, float scale,
                                  const int32_t* row_ptr, const int32_t* col_idx, int64_t col_len,
                                  void* o, float* lse, hipStream_t stream) {
-  return launch_attn_any<true>(d, blk, blk_k, q, k, v, B * H, N, n_pad, scale, row_ptr, col_idx,
-                               col_len, o, lse, stream);
+  return launch_attn_any<true, false>(d, blk, blk_k, q, k, v, B * H, N, n_pad, scale, row_ptr,
+                                      col_idx, col_len, o, lse, stream);
 }
 
 hipError_t launch_calibrate_f32(int d, int blk, int blk_k, const void* q, const void* k, int B,
@@ -818,8 +855,8 @@ hipError_t launch_construct_f32(int d, int blk, int blk_k, const void* q, const 
     err = masses(d, blk, blk_k, q, k, B * H, N, n_pad, scale, mass, scratch, stream);
   }
   if (err != hipSuccess) return err;
-  return launch_sparse_fwd_f32(d, blk, blk_k, q, k, v, B, H, N, n_pad, scale, nullptr, nullptr, 0,
-                               o, lse, stream);
+  return launch_attn_any<true, true>(d, blk, blk_k, q, k, v, B * H, N, n_pad, scale, nullptr,
+                                     nullptr, 0, o, lse, stream);
 }
 
 }  // namespace losa

@@ -51,7 +51,7 @@ hipError_t launch_sparse_fwd_bf16(int d, int blk, int blk_k, const void* q, cons
                                   const int32_t* row_ptr, const int32_t* col_idx,
                                   int64_t col_len, void* o, float* lse, void* workspace,
                                   hipStream_t stream);
-// dense attention over every valid key (row_ptr == nullptr for the f32 path)
+// dense attention over every valid key
 // stat != nullptr: also the block statistics [B*H][n_k][n_pad] (log2 units)
 hipError_t launch_dense_bf16(int d, int blk, int blk_k, const void* q, const void* k,
                              const void* v, int B, int H, int N, int n_pad, float scale, void* o,

@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 # (heads, d, block_q, block_k, N, dtype)
 CASES = [(52, 128, 128, 128, 577, "bf16"), (52, 64, 128, 32, 530, "bf16"),
-         (60, 64, 64, 64, 570, "bf16"), (40, 128, 64, 32, 545, "bf16")]
+         (60, 64, 64, 64, 570, "bf16"), (40, 128, 64, 32, 545, "bf16"),
+         (9, 64, 64, 64, 1024, "f32"), (12, 64, 64, 64, 385, "f32"),
+         (10, 128, 128, 128, 511, "f32"), (22, 128, 128, 32, 380, "f32")]
 
 
 @pytest.fixture(scope="module")

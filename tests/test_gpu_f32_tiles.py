@@ -1,8 +1,8 @@
 """fp32 kernels at the edges of their tiles.
 
-The attention kernel works on 32-row tiles, 256 at a time, and on 16-row tiles
-for a rest of 128 of the former or fewer (at d = 64 then throughout); its eight
-waves share a row's 32-key sub-tiles.  The masses come from block statistics in
+The attention kernel works on tiles of two groups of 16 rows, 256 at a time, and
+on tiles of one for a rest of 128 of the former or fewer (at d = 64 then
+throughout); its eight waves share a row's 32-key sub-tiles.  The masses come from block statistics in
 the construction step's output where there are no more key blocks than floats
 in a row of it, and else from a kernel that splits a row's key blocks over
 workgroups when the normalisers have room (the caller's lse, or that output)
