@@ -46,6 +46,8 @@
 // and carried in an fp64 running sum (and merged in fp64).  Added one by one
 // to an fp32 accumulator, the many small terms of far keys fall below half
 // its ulp and are lost: over 131k keys that biases the sum low by ~2e-4.
+#include <algorithm>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -567,14 +569,18 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// Block statistics of one query block over a range of key blocks:
-// stat[bh][j][q] = log2 of query q's unnormalised probability sum over block
-// j.  Waves and key blocks as in mass_f32_kernel.
+// Block statistics of one query block over a range of key blocks, for query
+// blocks i0 .. i0 + n_i - 1 of every head: for query q of these and key block j
+// its largest score, stat[bh][j][0][q] (log2 units), and the sum of its
+// probabilities against that maximum, stat[bh][j][1][q], carried across the
+// block's 32-key sub-tiles in fp64.  (One number, log2(sum) + maximum, has
+// no room for the sum's 24 bits beside the maximum's size.)  Waves and key blocks
+// as in mass_f32_kernel.
 template <int D, int BLK>
 __global__ void __launch_bounds__(256)
     stat_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
-                    float* __restrict__ stat, int bk_sub, int per_wg, int n_k, int n_kb, int N,
-                    int n_pad, float scale_log2) {
+                    float* __restrict__ stat, int i0, int n_i, int bk_sub, int per_wg, int n_k,
+                    int n_kb, int N, int n_pad, float scale_log2) {
   constexpr int M = 32;
   constexpr int RW = BLK / M;
   constexpr int KSP = 4 / RW;
@@ -585,13 +591,12 @@ __global__ void __launch_bounds__(256)
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rw = w % RW, sp = w / RW;
   const int lm = lane % M, g = lane / M;
-  const int n_q = n_pad / BLK;
-  const int bh = blockIdx.x / n_q;
-  const int i = blockIdx.x - bh * n_q;
+  const int bh = blockIdx.x / n_i;
+  const int i = blockIdx.x - bh * n_i;  // from i0
   const int bk = bk_sub * CK;
   const int j0 = blockIdx.y * per_wg + sp, j1 = min(n_kb, (int)(blockIdx.y + 1) * per_wg);
   if (j0 >= j1) return;
-  const int qrow = i * BLK + rw * M + lm;
+  const int qrow = (i0 + i) * BLK + rw * M + lm;
   const float* Kh = K + (size_t)bh * n_pad * D;
   f32x4_t qr[T::QI];
   load_q<D, M>(qr, Q + (size_t)bh * n_pad * D, qrow, g, qrow < N, scale_log2);
@@ -600,7 +605,8 @@ __global__ void __launch_bounds__(256)
   for (int c = 0; c < kLead; ++c) ring[c] = load_k<D, M>(Kh, j0 * bk, c, lm, g);
   for (int j = j0; j < j1; j += KSP) {
     // m: reference of the block's sum, the same in both lanes of a query
-    float m = kNegBig, l = 0.f;
+    float m = kNegBig;
+    double l = 0.0;
     const int subs = min(bk_sub, (N - j * bk + CK - 1) / CK);  // those that hold a valid key
     for (int u = 0; u < subs; ++u) {
       const int key0 = j * bk + u * CK;
@@ -611,31 +617,37 @@ __global__ void __launch_bounds__(256)
         ring[c % kLead] = load_k<D, M>(Kh, n < T::KC ? key0 : next, n % T::KC, lm, g);
       });
       const float m_new = fmaxf(m, tile_max<D, M>(s));
-      l = l * fast_exp2(m - m_new) + tile_exp<D, M>(s, m_new);
+      l = l * (double)fast_exp2(m - m_new) + (double)tile_exp<D, M>(s, m_new);
       m = m_new;
     }
-    const float sum = l + __shfl_xor(l, 32);
-    if (g == 0) stat[((size_t)bh * n_k + j) * n_pad + qrow] = __log2f(sum) + m;
+    const double sum = group_sum<M>(l);
+    if (g == 0) {
+      float* const at = stat + ((size_t)bh * n_k + j) * 2 * n_i * BLK + i * BLK + rw * M + lm;
+      at[0] = m;
+      at[n_i * BLK] = (float)sum;
+    }
   }
 }
 
-// Masses of one query block from its block statistics: each query's normaliser
-// over the n_kb key blocks (fp64 sums), then per key block the mean over the
-// valid queries.  Blocks past n_kb hold no valid key.
+// Masses of one query block from its block statistics: each query's maximum and
+// normaliser over the n_kb key blocks (fp64 sums), then per key block the mean
+// over the valid queries.  Blocks past n_kb hold no valid key.
 template <int BLK>
 __global__ void __launch_bounds__(256)
-    mass_of_stat_f32_kernel(const float* __restrict__ stat, float* __restrict__ mass, int n_k,
-                            int n_kb, int N, int n_pad) {
+    mass_of_stat_f32_kernel(const float* __restrict__ stat, float* __restrict__ mass, int i0,
+                            int n_i, int n_k, int n_kb, int N, int n_pad) {
   constexpr int PT = 256 / BLK;  // threads per query
   __shared__ float mx[256];
   __shared__ double sm[256];
-  __shared__ float lse2[BLK];
+  __shared__ float qmax[BLK], qinv[BLK];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int n_q = n_pad / BLK;
-  const int bh = blockIdx.x / n_q;
-  const int i = blockIdx.x - bh * n_q;
-  const float* base = stat + (size_t)bh * n_k * n_pad + i * BLK;
-  float* mrow = mass + (size_t)blockIdx.x * n_k;
+  const int bh = blockIdx.x / n_i;
+  const int i = i0 + blockIdx.x - bh * n_i;
+  const int row = n_i * BLK;  // floats of a row of statistics
+  const float* base = stat + (size_t)bh * n_k * 2 * row + (i - i0) * BLK;
+  const size_t step = 2 * (size_t)row;
+  float* mrow = mass + ((size_t)bh * n_q + i) * n_k;
   const int rows_valid = min(BLK, N - i * BLK);
   if (rows_valid <= 0) {
     for (int j = t; j < n_k; j += 256) mrow[j] = 0.f;
@@ -643,9 +655,10 @@ __global__ void __launch_bounds__(256)
   }
   const int q = t % BLK, part = t / BLK;
   float m = kNegBig;
-  for (int j = part; j < n_kb; j += PT) m = fmaxf(m, base[(size_t)j * n_pad + q]);
+  for (int j = part; j < n_kb; j += PT) m = fmaxf(m, base[j * step + q]);
   double l = 0.0;
-  for (int j = part; j < n_kb; j += PT) l += (double)fast_exp2(base[(size_t)j * n_pad + q] - m);
+  for (int j = part; j < n_kb; j += PT)
+    l += (double)base[j * step + row + q] * (double)fast_exp2(base[j * step + q] - m);
   mx[t] = m;
   sm[t] = l;
   __syncthreads();
@@ -656,7 +669,8 @@ __global__ void __launch_bounds__(256)
     double lt = 0.0;
 #pragma unroll
     for (int y = 0; y < PT; ++y) lt += sm[y * BLK + t] * (double)fast_exp2(mx[y * BLK + t] - mm);
-    lse2[t] = mm + __log2f((float)lt);
+    qmax[t] = mm;
+    qinv[t] = 1.0f / (float)lt;
   }
   __syncthreads();
   const float inv_rows = 1.0f / (float)rows_valid;
@@ -665,8 +679,9 @@ __global__ void __launch_bounds__(256)
     if (j < n_kb) {
 #pragma unroll
       for (int e = 0; e < BLK / 64; ++e) {
-        const int row = lane + 64 * e;
-        if (row < rows_valid) acc += fast_exp2(base[(size_t)j * n_pad + row] - lse2[row]);
+        const int x = lane + 64 * e;
+        if (x < rows_valid)
+          acc += base[j * step + row + x] * (fast_exp2(base[j * step + x] - qmax[x]) * qinv[x]);
       }
     }
     acc = wave_sum(acc);
@@ -767,23 +782,31 @@ hipError_t launch_mass(const void* q, const void* k, const float* lse2, float* m
   return hipGetLastError();
 }
 
-// Masses in one sweep over the keys: block statistics into `stat` ([BH][n_k]
-// [n_pad] floats), then their reduction.
+// Masses in one sweep over the keys: block statistics into `stat`, which has
+// room for `room` floats per query of the call, then their reduction.  They take 2
+// n_k floats per query, so where that is more than there are, the query blocks go
+// in two or three parts.
 template <int D, int BLK>
-hipError_t launch_stat(const void* q, const void* k, float* stat, float* mass, int BH, int blk_k,
-                       int N, int n_pad, float scale, hipStream_t stream) {
-  const int rows = BH * (n_pad / BLK);
+hipError_t launch_stat(const void* q, const void* k, float* stat, int room, float* mass, int BH,
+                       int blk_k, int N, int n_pad, float scale, hipStream_t stream) {
+  const int n_q = n_pad / BLK;
   const int n_k = n_pad / blk_k, n_kb = (N + blk_k - 1) / blk_k;
-  const int per_wg = key_blocks_per_wg(rows, n_kb, blk_k);
-  hipLaunchKernelGGL((stat_f32_kernel<D, BLK>), dim3(rows, (n_kb + per_wg - 1) / per_wg),
-                     dim3(256), 0, stream, static_cast<const float*>(q),
-                     static_cast<const float*>(k), stat, blk_k / CK, per_wg, n_k, n_kb, N, n_pad,
-                     scale * kLog2e);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(mass_of_stat_f32_kernel<BLK>, dim3(rows), dim3(256), 0, stream, stat, mass,
-                     n_k, n_kb, N, n_pad);
-  return hipGetLastError();
+  const int part = (int)std::min<int64_t>(n_q, (int64_t)n_q * room / (2 * n_k));
+  for (int i0 = 0; i0 < n_q; i0 += part) {
+    const int n_i = std::min(part, n_q - i0), rows = BH * n_i;
+    const int per_wg = key_blocks_per_wg(rows, n_kb, blk_k);
+    hipLaunchKernelGGL((stat_f32_kernel<D, BLK>), dim3(rows, (n_kb + per_wg - 1) / per_wg),
+                       dim3(256), 0, stream, static_cast<const float*>(q),
+                       static_cast<const float*>(k), stat, i0, n_i, blk_k / CK, per_wg, n_k, n_kb,
+                       N, n_pad, scale * kLog2e);
+    hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(mass_of_stat_f32_kernel<BLK>, dim3(rows), dim3(256), 0, stream, stat, mass,
+                       i0, n_i, n_k, n_kb, N, n_pad);
+    err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
+  return hipSuccess;
 }
 
 // Masses, given room for the log2 normalisers (one float per token; written
@@ -832,9 +855,10 @@ hipError_t launch_calibrate_f32(int d, int blk, int blk_k, const void* q, const 
 hipError_t launch_construct_f32(int d, int blk, int blk_k, const void* q, const void* k,
                                 const void* v, int B, int H, int N, int n_pad, float scale,
                                 void* o, float* mass, float* lse, hipStream_t stream) {
-  // O is written last: until then it holds the block statistics, one float per
-  // query and key block, where its d floats per query are enough for them, and
-  // the log2 normalisers otherwise (the masses then take a sweep of their own)
+  // O is written last: until then it holds the block statistics, two floats per
+  // query and key block, of all query blocks or a third of them and more, where
+  // there are d key blocks or fewer, and the log2 normalisers otherwise (the masses
+  // then take a sweep of their own)
   // (over an input it can hold neither: the mass kernel then finds its own
   // normalisers)
   const size_t bytes = (size_t)B * H * n_pad * d * sizeof(float);
@@ -845,7 +869,7 @@ hipError_t launch_construct_f32(int d, int blk, int blk_k, const void* q, const 
   if (scratch != nullptr && n_pad / blk_k <= d) {
 #define LOSA_F32_STAT(DD, BB) \
   if (d == DD && blk == BB)   \
-    err = launch_stat<DD, BB>(q, k, scratch, mass, B * H, blk_k, N, n_pad, scale, stream);
+    err = launch_stat<DD, BB>(q, k, scratch, d, mass, B * H, blk_k, N, n_pad, scale, stream);
     LOSA_F32_STAT(64, 64)
     LOSA_F32_STAT(64, 128)
     LOSA_F32_STAT(128, 64)
