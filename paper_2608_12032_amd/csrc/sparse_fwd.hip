@@ -769,11 +769,15 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, int B, int H,
   const int rows = BH * n_q;
   v = readable_v(v, o, (size_t)BH * n_pad * D * 2, workspace, stream);
   int* order = reinterpret_cast<int*>(static_cast<char*>(workspace) + order_offset(BH, n_pad, D));
-  if (rows <= (BLK == 64 ? 512 : 384)) {
-    // every row starts at once (or nearly), and the order kernel would be most
-    // of what the order gains: 272 rows of 34 blocks 71 us with it, 74 without,
-    // of 4 blocks 32 / 24; 512 rows of 64 blocks 138 / 147, of 6 blocks 52 / 47;
-    // 64-row blocks, 512 rows of 64: 57 / 51
+  if (rows <= (BLK == 64 && D == 128 ? 512 : 256)) {
+    // every wave has a SIMD to itself from the start (64-row blocks have two
+    // waves, but at d = 64 more of their workgroups gather on a CU), and the order
+    // could gain nothing for its launch: 256 rows of 32 blocks 67 us without, 70
+    // with it, of 4 blocks 13.7 / 16.5; 64-row blocks, d = 128, 512 rows of 64
+    // blocks 71 / 76, of 64 and 1 in turn 66 / 66.  With more rows two share a CU,
+    // and uneven ones in id order gather the long ones: 264 rows of 33 and 1 in
+    // turn 84 / 64, 384 rows of 48 and 1 125 / 93, d = 64 with 64-row blocks, 264
+    // rows 34 / 29.
     order = nullptr;
   } else {
     const int per_xcd = (rows + 7) / 8;

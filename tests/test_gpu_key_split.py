@@ -102,11 +102,12 @@ def test_output_over_v(L, H, N):
         assert got.data_ptr() == x.data_ptr() and torch.equal(got, want)
 
 
-@pytest.mark.parametrize("H,Cq,Ck,N", [(48, 128, 128, 1000), (64, 64, 64, 500)])
-def test_order_rule(L, H, Cq, Ck, N):
-    """The largest call whose rows run in id order against the first H heads of
-    one head more, which gets a dispatch order: the same bits."""
-    d = 128
+@pytest.mark.parametrize("H,Cq,Ck,N,d", [(48, 128, 128, 1000, 128), (64, 64, 64, 500, 128),
+                                         (32, 128, 128, 1000, 128), (32, 64, 32, 500, 64)])
+def test_order_rule(L, H, Cq, Ck, N, d):
+    """The largest call whose rows run in id order (64-row blocks at d = 128: 512
+    rows, else 256; or one that has a dispatch order like the next) against the first
+    H heads of one head more, which gets an order: the same bits."""
     n_pad = O.padded_len(N, Cq, Ck)
     n_q, n_k = n_pad // Cq, n_pad // Ck
     print(f"[gpu-key-split] order rule: {H * n_q} rows", flush=True)
