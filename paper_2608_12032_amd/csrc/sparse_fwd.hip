@@ -521,7 +521,7 @@ __global__ void __launch_bounds__(BLK * 2)
       load_k(y, jy, y % NS);
       if (y < R - 2) load_v(y, jy, y % NS);
     }
-    for (int x = tid * 16; x < C::SUB; x += NT * 16)
+    for (int x = (w * 64 + lane) * 16; x < C::SUB; x += NT * 16)
       *reinterpret_cast<f32x4_t*>(smem + C::RING + (R - 1) * C::SUB + x) = f32x4_t{};
 #pragma unroll
     for (int a2 = 0; a2 < 2; ++a2)
