@@ -116,7 +116,9 @@ struct FwdCfg {
   static_assert(SUB % (1024 * NW) == 0, "sub-tile must split into whole wave loads");
   static_assert(R % NS == 0 && R >= 4 && (R & 1) == 0, "ring holds whole key blocks");
   static_assert(KS == 2 * DB, "QK and PV steps alternate one to one");
-  static_assert(2 * RING >= kMaxList, "list-building scratch fits the rings");
+  // list-building scratch: block flags from byte 0, wave flags in V slot 2
+  static constexpr int WFLAG = RING + 2 * SUB;
+  static_assert(WFLAG >= kMaxList, "the block flags end before the wave flags");
 };
 
 // Swizzled chunk of K chunk c in sub-tile row `row`.
@@ -393,8 +395,8 @@ __global__ void __launch_bounds__(BLK * 2)
     // at 156 rows of 12)
     // (the waves' flags lie in the V slot that no load writes before the
     // pipeline's first barrier: 8 bytes more LDS would cost d = 64 with 64-row
-    // blocks its fourth workgroup per CU, 41 against 31 us at 1,024 rows)
-    int* const wcount = reinterpret_cast<int*>(smem + C::RING + 2 * C::SUB);
+    // blocks its fourth workgroup per CU: 1,024 rows of 16 blocks 40 us, not 30)
+    int* const wcount = reinterpret_cast<int*>(smem + C::WFLAG);
     const int len = (int)(e1 - e0 < n_k ? e1 - e0 : n_k);
     bool sorted = e1 - e0 <= n_k;
     for (int x = tid; x < len; x += NT) {
@@ -403,8 +405,8 @@ __global__ void __launch_bounds__(BLK * 2)
       sorted = sorted && j > before && j < n_k;
       list[x] = (uint16_t)j;
     }
-    if (lane == 0) wcount[w] = 1;
-    if (!sorted) wcount[w] = 0;
+    const bool wave_sorted = __ballot(!sorted) == 0;
+    if (lane == 0) wcount[w] = wave_sorted;
     __syncthreads();
     bool use = true;
 #pragma unroll
