@@ -156,8 +156,15 @@ def workspace_bytes(which: int, dtype_code: int, B, H, N, d, block_q, block_k) -
     return int(lib.losa_workspace_bytes(which, dtype_code, B, H, N, d, block_q, block_k))
 
 
-# the same numbers, kept: a call with a workspace asks for its size each time
-_need = functools.lru_cache(maxsize=1024)(workspace_bytes)
+_kept = functools.lru_cache(maxsize=1024)(workspace_bytes)
+_INTS = (int,) * 8
+
+
+def _need(*args) -> int:
+    """The same numbers, kept: a call with a workspace asks for its size each
+    time.  Only for plain ints, which are their values: a size held in a tensor is
+    hashed by identity, whatever it holds later, and one in an array not at all."""
+    return (_kept if tuple(map(type, args)) == _INTS else workspace_bytes)(*args)
 
 
 def losa_calibrate_mass(q, k, N: int, block_q: int, block_k: int | None = None,

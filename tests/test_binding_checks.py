@@ -2,6 +2,7 @@
 the library (which cannot tell a host pointer, a wrong element type or a short
 buffer from a valid one).  The host-tensor cases run on the CPU; the rest need
 device tensors and are marked gpu (nothing is launched in them)."""
+import numpy as np
 import pytest
 import torch
 
@@ -22,6 +23,20 @@ def test_host_tensors_are_rejected(L):
     mass = torch.zeros((1, 2, 1, 1))
     with pytest.raises(ValueError, match="must live on"):
         L.losa_select_blocks(mass, 100, 128, 128, 0.99)
+
+
+def test_sizes_held_in_arrays_and_tensors(L):
+    """Whatever ctypes takes as an int is a size: an array, or a tensor that
+    holds another value at the next call."""
+    def args(n):
+        return 2, L.LOSA_DTYPE_BF16, 1, 2, n, 64, 64, 64
+
+    for n in (300, np.int64(300), np.array(300), torch.tensor(300)):
+        assert L._need(*args(n)) == L.workspace_bytes(*args(300))
+    n = torch.tensor(300)
+    for value in (300, 3000):
+        n.fill_(value)
+        assert L._need(*args(n)) == L.workspace_bytes(*args(value))
 
 
 @pytest.mark.gpu
