@@ -36,7 +36,13 @@
  *   block_k either equal to block_q or 32 (the paper's rectangular setting,
  *   Sec. 5.1: 128-row query blocks, 32-key key blocks).  Other valid
  *   combinations return LOSA_ERR_UNSUPPORTED.
- * - Calls are deterministic: the same inputs give bitwise identical outputs.
+ * - Calls are deterministic: the same inputs give bitwise identical outputs, and
+ *   a head gives the same bits alone and among other heads.
+ * - Memory.  An output shares no memory with another output, the workspace or an
+ *   input, except o with q (the same address), and bf16 o with v (anywhere).  An
+ *   o over k, or over v in f32, is not detected: rows still to come would read
+ *   what finished rows have written.  f32 losa_construct uses o as scratch before
+ *   it writes it (not where it overlaps an input).
  */
 #ifndef LOSA_H
 #define LOSA_H
@@ -99,7 +105,8 @@ typedef enum {
  * Arithmetic: bf16 inputs use bf16 matrix-core products with fp32
  * accumulation; f32 inputs use fp32 arithmetic, with each query's softmax
  * normaliser carried across 32-key chunks in fp64.  Both bf16 schemes compute
- * the same scores; their masses differ only by fp32 rounding.
+ * the same scores; their masses differ only by fp32 rounding, as do f32 masses
+ * with and without lse.
  */
 losa_status losa_calibrate_mass(const void* q, const void* k, losa_dtype dtype, int B, int H,
                                 int N, int d, int block_q, int block_k, float scale, float* mass,
@@ -265,7 +272,10 @@ losa_status losa_sparse_attn_fwd_noalloc(const void* q, const void* k, const voi
  * separate calls would cost a dense attention plus the calibration's sweeps
  * over Q K^T.  o equals losa_sparse_attn_fwd over a full support bitwise;
  * mass and lse agree with losa_calibrate_mass to fp32 rounding.
- * f32 runs losa_calibrate_mass and a dense fp32 forward.
+ * f32 forms the masses first and then runs a dense fp32 forward.  The masses
+ * take one sweep over the keys where n_k <= d and o overlaps no input (o then
+ * holds two floats per query and key block until it is written), else two; mass
+ * and lse agree with losa_calibrate_mass to fp32 rounding.
  */
 losa_status losa_construct(const void* q, const void* k, const void* v, losa_dtype dtype, int B,
                            int H, int N, int d, int block_q, int block_k, float scale, void* o,

@@ -381,7 +381,7 @@ losa_status losa_construct(const void* q, const void* k, const void* v, losa_dty
                 losa::kSparseFwdMaxNk);
   hipStream_t hs = static_cast<hipStream_t>(stream);
   if (dtype == LOSA_DTYPE_F32) {
-    // fp32: two sweeps over the keys for the masses, then the dense forward
+    // fp32: the masses (one sweep over the keys or two), then the dense forward
     return hip_status(losa::launch_construct_f32(d, block_q, block_k, q, k, v, B, H, N, s.n_pad,
                                                  scale, o, mass, lse, hs),
                       "losa_construct");

@@ -60,8 +60,8 @@
 // kernel of its own before each call (33 us at 12 heads x 32,768 x 128).  The
 // forward itself pays 0.6 to 1.4 % for twice the V read instructions: whole
 // calls 2,962 -> 2,949 us (Wan shape), 2,904 -> 2,863 (32-key blocks), 3,132 ->
-// 3,108 (CogVideoX), 291 -> 260 (Wan, 2.7 % of the blocks), 33.6 -> 28.4 (1,560
-// tokens); HunyuanVideo 64.6 -> 64.8 ms.
+// 3,108 (CogVideoX), 291 -> 260 (Wan, 2.7 % of the blocks); HunyuanVideo 64.6 ->
+// 64.8 ms.
 //
 // Softmax.  Probabilities are taken against the running max without looking
 // at the sub-tile's scores first; only when a lane's sub-tile sum exceeds
@@ -76,7 +76,8 @@
 //
 // Dispatch order (sparse mode).  Rows run longest first inside chunks of
 // neighbouring query blocks, each XCD on a contiguous range of rows
-// (order_rows_kernel), so rows in flight share their key blocks in L2.
+// (order_rows_kernel), so rows in flight share their key blocks in L2; calls whose
+// waves all have a SIMD to themselves run in id order (launch_fwd).
 //
 // Padding.  Keys >= N get score -inf (only the ragged last block needs it).
 // Query rows >= N are written as 0 with lse = -inf; so are rows with an empty
@@ -319,8 +320,9 @@ constexpr float kSumBound = 1048576.0f;
 // d = 128 (output accumulators, Q operands and two score tiles take ~250
 // registers); four at d = 64, where a wave's VALU work per MFMA is twice that
 // of d = 128 and more waves hide more of it (128 registers; the rings and
-// block list, 40 KiB per workgroup, allow four).  Against three waves at the CogVideoX shape: 3,004 -> 2,975 us,
-// 3,051 -> 2,953 with 32-key blocks.  64-row blocks are limited by LDS instead.
+// block list, 40 KiB per workgroup, allow four).  Three waves, whose registers
+// allow operand reads to lead by four MFMAs: 3,178 us a call at the CogVideoX
+// shape, four with a lead of two 3,090.  64-row blocks are limited by LDS instead.
 // (Dense with 32-key blocks keeps three waves: it also stores a statistic per
 // sub-tile, and at 128 registers one would spill.)
 template <int D, int BLK, int BK, bool DENSE>

@@ -102,6 +102,27 @@ def test_output_over_v(L, H, N):
         assert got.data_ptr() == x.data_ptr() and torch.equal(got, want)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("H,N", [(2, 600), (40, 1000)])   # few rows and many
+def test_output_over_q(L, H, N, dtype):
+    """o written over q gives what separate buffers give, in every forward call."""
+    n_pad = O.padded_len(N, 128, 128)
+    n = n_pad // 128
+    print(f"[gpu-key-split] o over q, {H} heads, {dtype}", flush=True)
+    g = torch.Generator().manual_seed(78)
+    q, k, v = (torch.randn((1, H, n_pad, 128), generator=g).to(dtype).cuda() for _ in range(3))
+    rp = (torch.arange(H * n + 1) * n).int().cuda()
+    ci = torch.arange(n, dtype=torch.int32).repeat(H * n).cuda()
+    want = L.losa_sparse_attn_fwd(q, k, v, N, 128, 128, rp, ci)
+    for call in (lambda x: L.losa_sparse_attn_fwd(x, k, v, N, 128, 128, rp, ci, out=x),
+                 lambda x: L.losa_sparse_attn_fwd_noalloc(x, k, v, N, 128, 128, rp, ci, out=x),
+                 lambda x: L.losa_construct(x, k, v, N, 128, 128, out=x)[0]):
+        x = q.clone()
+        got = call(x)
+        torch.cuda.synchronize()
+        assert got.data_ptr() == x.data_ptr() and torch.equal(got, want)
+
+
 @pytest.mark.parametrize("H,Cq,Ck,N,d", [(48, 128, 128, 1000, 128), (64, 64, 64, 500, 128),
                                          (32, 128, 128, 1000, 128), (32, 64, 32, 500, 64)])
 def test_order_rule(L, H, Cq, Ck, N, d):
