@@ -33,8 +33,8 @@
 // instructions against one of 32 on 32x32x2, whose rows round differently from
 // those of a 16-row tile: 2 % slower at d = 128 (1,090 / 1,072 us at 12 x 4,437),
 // 4 % faster at d = 64 (590 / 614).
-// The construction step's masses take one sweep over the keys (175 us at N =
-// 4,437 x 4 heads and 11 us for their reduction; two sweeps: 238 + 175).
+// The construction step's masses take one sweep over the keys (186 us at N =
+// 4,437 x 4 heads and 15 us for their reduction; the calibration's two: 421).
 //
 // Masking and padding follow the bf16 kernels: keys >= N never enter a
 // softmax, query rows >= N read Q as 0 and get O = 0 and lse = -inf, and so do
@@ -785,7 +785,8 @@ hipError_t launch_mass(const void* q, const void* k, const float* lse2, float* m
 // Masses in one sweep over the keys: block statistics into `stat`, which has
 // room for `room` floats per query of the call, then their reduction.  They take 2
 // n_k floats per query, so where that is more than there are, the query blocks go
-// in two or three parts.
+// in parts (two at most: n_k <= room, and `part` is a whole number of blocks for
+// every block shape).
 template <int D, int BLK>
 hipError_t launch_stat(const void* q, const void* k, float* stat, int room, float* mass, int BH,
                        int blk_k, int N, int n_pad, float scale, hipStream_t stream) {
@@ -856,7 +857,7 @@ hipError_t launch_construct_f32(int d, int blk, int blk_k, const void* q, const 
                                 const void* v, int B, int H, int N, int n_pad, float scale,
                                 void* o, float* mass, float* lse, hipStream_t stream) {
   // O is written last: until then it holds the block statistics, two floats per
-  // query and key block, of all query blocks or a third of them and more, where
+  // query and key block, of all query blocks or one half and then the other, where
   // there are d key blocks or fewer, and the log2 normalisers otherwise (the masses
   // then take a sweep of their own)
   // (over an input it can hold neither: the mass kernel then finds its own

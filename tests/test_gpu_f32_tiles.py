@@ -4,7 +4,7 @@ The attention kernel works on tiles of two groups of 16 rows, 256 at a time, and
 on tiles of one for a rest of 128 of the former or fewer (at d = 64 then
 throughout); its eight waves share a row's 32-key sub-tiles.  The masses come from block statistics in
 the construction step's output (two floats per query and key block, the query
-blocks in up to three parts) where there are no more key blocks than floats in a
+blocks in up to two parts) where there are no more key blocks than floats in a
 row of it, and else from a kernel that splits a row's key blocks over
 workgroups when the normalisers have room (the caller's lse, or that output)
 and sweeps the keys itself when they have none.  Each combination of tile height, head size, block
